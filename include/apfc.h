@@ -180,9 +180,9 @@ size_t apfc_workspace_bytes(const apfc_ctx* ctx);
  * stay valid until the context is destroyed or another workspace is attached. */
 int apfc_set_workspace(apfc_ctx* ctx, void* device_ptr, size_t bytes);
 
-/* zeta_j = M^{-1} G_j eta_j for every instance (the initial auxiliary field of Algorithm 1),
- * computed by 60 (2D) / 100 (3D) Chebyshev-Jacobi iterations with the exact spectral bounds of the
- * Jacobi-scaled mass matrix (error below 1e-15 relative). states[count]. */
+/* zeta_j = M^{-1} G_j eta_j for every instance (the initial auxiliary field of Algorithm 1): on the uniform
+ * periodic mesh M^{-1} G_j is a sum of one line filter per direction, applied to FP64 rounding.
+ * states[count]. */
 int apfc_init_zeta(apfc_ctx* ctx, apfc_state* states, void* stream);
 
 /* One time step of Algorithm 1 for every instance: eta, zeta <- eta^m, zeta^m.  source is

@@ -110,6 +110,7 @@ struct Dev {
     const Tile* mtiles = nullptr;    // device [nmtiles]: bricks of the separable mass inverse
     int nmtiles = 0, mbz = kBrickZShallow;   // brick depth in planes (3D)
     int ntiles = 0, nchunks = 0, S = 0, TY = 16, J = 0, count = 0, dim = 2;
+    int maxn[3] = {1, 1, 1};         // largest mesh sizes over the systems
     long long NT = 0;                // half-vector length (complex values)
     Terms terms{};
     Probe* probe = nullptr;
@@ -260,8 +261,8 @@ void launch_xupdate(const Dev& d, const cx<T>* Z, long long zstride, const int* 
 void launch_cycle_start(const Dev& d, const Krylov& kr, const double* part, bool first, int* pub, hipStream_t st);
 void launch_solve_y(const Dev& d, const Krylov& kr, hipStream_t st);
 
-void launch_mass_solve(const Dev& d, const zd* eta, zd* zeta, zd* r, zd* p0, zd* p1, zd* q, double* part,
-                       int iters, hipStream_t st);
+// zeta = M^{-1} G eta of every system (kernels_mass.hip)
+void launch_zeta(const Dev& d, const zd* eta, zd* zeta, hipStream_t st);
 // One multigrid V-cycle x = V(b) for L on every system (kernels_mg.hip); fine-level work buffers r, d0, d1.
 template <typename T>
 void launch_mg_vcycle(const Dev& fine, const MgLevels& mg, const cx<T>* b, cx<T>* x, cx<T>* r, cx<T>* d0, cx<T>* d1,

@@ -132,6 +132,7 @@ struct apfc_ctx {
     int cheb_shape = 0;
     size_t max_ctiles = 0;
     long long NT = 0, NI = 0;
+    int maxn[3] = {1, 1, 1};           // largest mesh sizes over the systems
     int TY = 16;
     int max_tiles = 0;
     double dt = -1.0;
@@ -216,6 +217,7 @@ struct apfc_ctx {
         d.J = J;
         d.count = count;
         d.dim = dim;
+        for (int q = 0; q < 3; ++q) d.maxn[q] = maxn[q];
         d.NT = NT;
         d.terms = terms;
         d.probe = probe.target != KID_NONE ? &probe : nullptr;
@@ -905,6 +907,11 @@ int apfc_create_batch(int count, const apfc_mesh* meshes, const apfc_lattice* la
     }
     c->NT = off;
     c->NI = doff;
+    for (const Sys& y : c->sys) {
+        c->maxn[0] = std::max(c->maxn[0], y.nx);
+        c->maxn[1] = std::max(c->maxn[1], y.ny);
+        c->maxn[2] = std::max(c->maxn[2], y.nz);
+    }
     for (int s = 0; s < c->S; ++s) {
         Sys& y = c->sys[s];
         y.cbeg = (int)c->chunks.size();
@@ -1471,8 +1478,7 @@ int apfc_init_zeta(apfc_ctx* c, apfc_state* states, void* stream) {
     Dev d = c->dev();
     d.probe = nullptr;
     launch_state_in(d, tab(c, 0), nullptr, c->X, st);
-    const int it = c->dim == 2 ? 60 : 100;
-    launch_mass_solve(d, c->X + c->NT, c->R, c->R + c->NT, c->W, c->W + c->NT, c->B, c->tpart, it, st);
+    launch_zeta(d, c->X + c->NT, c->R, st);
     launch_planar_out(d, c->R, tab(c, 1), st);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
@@ -1490,8 +1496,7 @@ int apfc_energy(apfc_ctx* c, const apfc_state* states, double* host_out, void* s
     Dev d = c->dev();
     d.probe = nullptr;
     launch_state_in(d, tab(c, 0), nullptr, c->X, st);
-    const int it = c->dim == 2 ? 60 : 100;
-    launch_mass_solve(d, c->X + c->NT, c->R, c->R + c->NT, c->W, c->W + c->NT, c->B, c->tpart, it, st);
+    launch_zeta(d, c->X + c->NT, c->R, st);
     launch_energy_parts(d, c->X + c->NT, c->R, c->tpart, st);
     launch_reduce(d, c->tpart, kE0, 2, false, c->kr.redr, kSlots, nullptr, st);
     HIPCHK(hipMemcpyAsync(c->h_dbl, c->kr.redr, sizeof(double) * kSlots * c->S, hipMemcpyDeviceToHost, st));
@@ -1499,7 +1504,7 @@ int apfc_energy(apfc_ctx* c, const apfc_state* states, double* host_out, void* s
     for (int b = 0; b < c->count; ++b) {
         double e = 0.0;
         for (int j = 0; j < c->J; ++j) e += c->h_dbl[(b * c->J + j) * kSlots + 0];
-        e += c->h_dbl[(b * c->J) * kSlots + 1];
+        for (int j = 0; j < c->J; ++j) e += c->h_dbl[(b * c->J + j) * kSlots + 1];
         host_out[b] = e;
     }
     return APFC_OK;
@@ -1520,14 +1525,17 @@ int apfc_energy_grad(apfc_ctx* c, const apfc_state* states, double* const* grad,
     Dev d = c->dev();
     d.probe = nullptr;
     launch_state_in(d, tab(c, 0), nullptr, c->X, st);
-    const int it = c->dim == 2 ? 60 : 100;
-    launch_mass_solve(d, c->X + c->NT, c->R, c->R + c->NT, c->W, c->W + c->NT, c->B, c->tpart, it, st);
+    launch_zeta(d, c->X + c->NT, c->R, st);
     launch_energy_grad(d, c->X + c->NT, c->R, tab(c, 1), c->tpart, st);
     launch_reduce(d, c->tpart, kE1, 1, false, c->kr.redr, kSlots, nullptr, st);
     HIPCHK(hipMemcpyAsync(c->h_dbl, c->kr.redr, sizeof(double) * kSlots * c->S, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (ddB)
-        for (int b = 0; b < c->count; ++b) ddB[b] += c->h_dbl[(b * c->J) * kSlots];
+        for (int b = 0; b < c->count; ++b) {
+            double dd = 0.0;
+            for (int j = 0; j < c->J; ++j) dd += c->h_dbl[(b * c->J + j) * kSlots];
+            ddB[b] += dd;
+        }
     return APFC_OK;
 }
 

@@ -77,31 +77,9 @@ __device__ __forceinline__ zd factor(const Terms& T, int t, int q, const zd* eta
     return T.cj[t][q] ? cconj(v) : v;
 }
 
-// d = dF_j = 2 a1/a0 + 4 (a2/a0) A (same for every j), h_j = F^s_j - d eta_j.
-__device__ __forceinline__ void bulk_h(const Terms& T, const Sys& s, const zd* eta, double& d, zd* h) {
-    const int J = T.J;
-    double A = 0.0;
-    for (int l = 0; l < J; ++l) A += abs2(eta[l]);
-    A *= 2.0;
-    d = 2.0 * s.a1 / s.a0 + 4.0 * s.a2 / s.a0 * A;
-    const double c4 = -4.0 * s.a2 / s.a0;
-    for (int l = 0; l < J; ++l) h[l] = (c4 * abs2(eta[l])) * eta[l];
-    for (int t = 0; t < T.n; ++t) {
-        const double c = term_coef(T, t, s);
-        const int ord = T.order[t];
-        for (int q = 0; q < ord; ++q) {
-            zd p{c, 0.0};
-            for (int r = 0; r < ord; ++r)
-                if (r != q) p = cmul(p, factor(T, t, r, eta));
-            const int l = T.idx[t][q];
-            h[l] = h[l] + (T.cj[t][q] ? p : cconj(p));
-        }
-    }
-}
-
-// bulk_h with the amplitudes in registers: JM >= T.J compile-time slots (eta zero beyond T.J), the
-// amplitude of a resonant factor picked by unrolled selects instead of a run-time array index, so nothing
-// goes through scratch memory.  Same operations in the same order as bulk_h.
+// d = dF_j = 2 a1/a0 + 4 (a2/a0) A (same for every j), h_j = F^s_j - d eta_j, with the amplitudes in
+// registers: JM >= T.J compile-time slots (eta zero beyond T.J), the amplitude of a resonant factor picked by
+// unrolled selects instead of a run-time array index, so nothing goes through scratch memory.
 template <int JM>
 __device__ __forceinline__ zd pick(const zd (&e)[JM], int k) {
     zd r = e[0];
@@ -152,10 +130,11 @@ __device__ __forceinline__ void bulk_h_reg(const Terms& T, const Sys& s, const z
     }
 }
 
-__device__ __forceinline__ double bulk_f(const Terms& T, const Sys& s, const zd* eta) {
-    const int J = T.J;
+template <int JM>
+__device__ __forceinline__ double bulk_f_reg(const Terms& T, const Sys& s, const zd (&eta)[JM]) {
     double A = 0.0, S4 = 0.0;
-    for (int l = 0; l < J; ++l) {
+#pragma unroll
+    for (int l = 0; l < JM; ++l) {
         const double a = abs2(eta[l]);
         A += a;
         S4 += a * a;
@@ -163,8 +142,14 @@ __device__ __forceinline__ double bulk_f(const Terms& T, const Sys& s, const zd*
     A *= 2.0;
     double f = s.a1 / s.a0 * A + s.a2 / s.a0 * (A * A - 2.0 * S4);
     for (int t = 0; t < T.n; ++t) {
+        const int ord = T.order[t];
         zd p{1.0, 0.0};
-        for (int r = 0; r < T.order[t]; ++r) p = cmul(p, factor(T, t, r, eta));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q >= ord) break;
+            const zd v = pick(eta, T.idx[t][q]);
+            p = cmul(p, T.cj[t][q] ? cconj(v) : v);
+        }
         f += 2.0 * term_coef(T, t, s) * p.x;
     }
     return f;
@@ -487,14 +472,13 @@ __global__ __launch_bounds__(kBlock) void k_pc_final(const Sys* sys, const Tile*
 // Same recurrence as k_cheb2d, with the scalars of iteration j from the system's table (Sys::cb).
 // ------------------------------------------------------------------------------------------
 
-// r0 of the inner solve (STAGE 0: beta1; 1: beta2 - kappa G x1; 2: M x2; 3: G src for the accurate
-// mass solve M zeta = G eta), d0 = r0/(theta D), x = d0
+// r0 of the inner solve (STAGE 0: beta1; 1: beta2 - kappa G x1; 2: M x2), d0 = r0/(theta D), x = d0
 template <int DIM, int TY, typename T, int STAGE>
 __global__ __launch_bounds__(kBlock) void k_cb_init(const Sys* sys, const Tile* tiles, const int* mask, const cx<T>* v,
                                                    const cx<T>* src, cx<T>* r, cx<T>* d, cx<T>* xv, long long NT) {
     TILE_PROLOGUE();
-    constexpr bool isM = STAGE == 0 || STAGE == 3;
-    constexpr bool WG = STAGE == 1 || STAGE == 3;
+    constexpr bool isM = STAGE == 0;
+    constexpr bool WG = STAGE == 1;
     const T scale = T(sys[tile.sys].cb[isM ? 0 : 1][0][0]);
     FOR_ROWS(TY) {
         Nbr<DIM> n;
@@ -510,8 +494,6 @@ __global__ __launch_bounds__(kBlock) void k_cb_init(const Sys* sys, const Tile* 
                 T(s.kv[0]), T(s.kv[1]), T(s.kv[2]), Mu, Ku, Tu);
             if constexpr (STAGE == 1)
                 rv = ld<T>(v, NT + i) - T(s.kappa) * gop(Ku, Tu);
-            else if constexpr (STAGE == 3)
-                rv = gop(Ku, Tu);
             else
                 rv = Mu;
         }
@@ -547,18 +529,17 @@ __global__ __launch_bounds__(kBlock) void k_cb_iter(const Sys* sys, const Tile* 
     }
 }
 
-// 3D versions of k_cb_init (STAGE 1..3, the stages with a stencil) and k_cb_iter on z-marching
+// 3D versions of k_cb_init (STAGE 1 and 2, the stages with a stencil) and k_cb_iter on z-marching
 // bricks; same arithmetic per node.
 // RR planes per thread on bricks of 64 x BY columns (64 x BY threads).
 template <int RR, int BY, typename T, int STAGE>
 __global__ __launch_bounds__(64 * BY) void k_cb_init3d(const Sys* sys, const Tile* tiles, const int* mask,
                                                       const cx<T>* v, const cx<T>* src, cx<T>* r, cx<T>* d, cx<T>* xv,
                                                       long long NT) {
-    static_assert(STAGE >= 1 && STAGE <= 3, "stage 0 has no stencil");
+    static_assert(STAGE == 1 || STAGE == 2, "stage 0 has no stencil");
     TILE_PROLOGUE();
-    constexpr bool isM = STAGE == 3;
-    constexpr bool WG = STAGE == 1 || STAGE == 3;
-    const T scale = T(sys[tile.sys].cb[isM ? 0 : 1][0][0]);
+    constexpr bool WG = STAGE == 1;
+    const T scale = T(sys[tile.sys].cb[1][0][0]);
     const int y = tile.y0 + ty;
     const T h = T(s.h), m0 = h * T(1.0 / 6.0), m1 = h * T(4.0 / 6.0), ih = T(1) / h;
     const T k0 = T(s.kv[0]), k1 = T(s.kv[1]), k2 = T(s.kv[2]);
@@ -573,8 +554,6 @@ __global__ __launch_bounds__(64 * BY) void k_cb_init3d(const Sys* sys, const Til
             cx<T> rv;
             if constexpr (STAGE == 1)
                 rv = ld<T>(v, NT + i) - T(s.kappa) * gop(Ku, Tu);
-            else if constexpr (STAGE == 3)
-                rv = gop(Ku, Tu);
             else
                 rv = Mu;
             const cx<T> dv = scale * rv;
@@ -1112,31 +1091,47 @@ __global__ void k_solve_y(Krylov kr, int S) {
 // ------------------------------------------------------------------------------------------
 // energy, its gradient, adjoint pieces
 // ------------------------------------------------------------------------------------------
-// per tile: E0 = sum 2 Re(zeta^H G eta) - zeta^H M zeta (= eta^H G M^{-1} G eta to second order
-// in the error of zeta); E1 = sum w f^s(eta) on the amplitude-0 tiles of each instance.
-template <int DIM, int TY>
+// Per tile: E0 = sum zeta^H M zeta (zeta = M^{-1} G eta to rounding) and E1 = sum w f^s(eta).  The J tiles of an
+// instance that cover the same nodes share the nodal part (amplitude j's tile takes the row steps rr with
+// rr % J == j, as in k_nonlinear).  3D: the planes of zeta staged in LDS (one load per node instead of 27).
+template <int DIM, int TY, int JM>
 __global__ __launch_bounds__(kBlock) void k_energy(const Sys* sys, const Tile* tiles, const Terms T, const zd* eta,
                                                   const zd* zeta, double* part, int ntiles) {
     __shared__ double lds[8];
     const int* mask = nullptr;
     TILE_PROLOGUE();
     double acc[2] = {0.0, 0.0};
-    FOR_ROWS(TY) {
-        Nbr<DIM> n;
-        make_nbr<DIM>(s, x, y, pz, n);
-        zd Me, Ke, Te, Mz, Kz, Tz;
-        stencil<DIM, true, true, double>([&](int a, int b, int c) { return eta[s.off + nb_index<DIM>(n, a, b, c)]; },
-                                         s.h, s.kv[0], s.kv[1], s.kv[2], Me, Ke, Te);
-        stencil<DIM, false, false, double>(
-            [&](int a, int b, int c) { return zeta[s.off + nb_index<DIM>(n, a, b, c)]; }, s.h, 0.0, 0.0, 0.0, Mz,
-            Kz, Tz);
-        const long long il = nb_index<DIM>(n, 1, 1, 1);
-        const zd zc = zeta[s.off + il];
-        acc[0] += 2.0 * cdot(zc, gop(Ke, Te)).x - cdot(zc, Mz).x;
-        if (s.j == 0) {
-            zd e[kMaxJ];
-            for (int l = 0; l < T.J; ++l) e[l] = eta[s.off + l * s.N + il];
-            acc[1] += s.w * bulk_f(T, s, e);
+    const long long o0 = s.off - (long long)s.j * s.N;     // amplitude 0 of the instance
+    auto at = [&](int rr, long long il, zd zc, zd Mz) {
+        acc[0] += cdot(zc, Mz).x;
+        if (rr % T.J != s.j) return;
+        zd e[JM];
+#pragma unroll
+        for (int l = 0; l < JM; ++l) e[l] = l < T.J ? eta[o0 + l * s.N + il] : zd{0.0, 0.0};
+        acc[1] += s.w * bulk_f_reg<JM>(T, s, e);
+    };
+    if constexpr (DIM == 3) {
+        const int y = tile.y0 + ty;
+        const double m0 = s.h / 6.0, m1 = 4.0 * s.h / 6.0;
+        __shared__ zd buf[2][1][kPP];
+        zmarch_lds<TY / 4, 1, false, false, double, double>(
+            s, tile, (int)(threadIdx.x & 63), ty, buf, m0, m1, 0.0, [&](int, long long i) { return zeta[s.off + i]; },
+            [&](int z, const auto& P) {
+                if (x >= s.nx || y >= s.ny || z >= s.nz) return;
+                zd Mz, Kz, Tz;
+                zcombine<false, false, double>(P[0][0], P[0][1], P[0][2], m0, m1, 0.0, 0.0, 0.0, 0.0, Mz, Kz, Tz);
+                at(z - tile.z, ((long long)z * s.ny + y) * s.nx + x, P[0][1].c, Mz);
+            });
+    } else {
+        FOR_ROWS(TY) {
+            Nbr<DIM> n;
+            make_nbr<DIM>(s, x, y, pz, n);
+            zd Mz, Kz, Tz;
+            stencil<DIM, false, false, double>(
+                [&](int a, int b, int c) { return zeta[s.off + nb_index<DIM>(n, a, b, c)]; }, s.h, 0.0, 0.0, 0.0, Mz,
+                Kz, Tz);
+            const long long il = nb_index<DIM>(n, 1, 1, 1);
+            at(rr_, il, zeta[s.off + il], Mz);
         }
     }
     block_sum<2>(acc, lds);
@@ -1146,37 +1141,78 @@ __global__ __launch_bounds__(kBlock) void k_energy(const Sys* sys, const Tile* t
     }
 }
 
-// grad_j = 2 (w F^s_j(eta) + G_j zeta_j) (planar output); partial of dE/dDeltaB = sum w A/(2 a0).
+// grad_j = 2 (w F^s_j(eta) + G_j zeta_j) (planar output) in two passes: 2 G_j zeta_j (3D: plane march through LDS),
+// then the nodal part, evaluated once per node for every amplitude (the J tiles of an instance share the rows as
+// in k_nonlinear; evaluated by every amplitude's tile, J times over, it was 9/10 of the call), with the partial of
+// dE/dDeltaB = sum w A/(2 a0).
 template <int DIM, int TY>
-__global__ __launch_bounds__(kBlock) void k_energy_grad(const Sys* sys, const Tile* tiles, const Terms T,
-                                                       const zd* eta, const zd* zeta, double* const* grad_tab,
-                                                       double* part, int ntiles) {
-    __shared__ double lds[4];
+__global__ __launch_bounds__(kBlock) void k_energy_grad(const Sys* sys, const Tile* tiles, const zd* zeta,
+                                                       double* const* grad_tab) {
     const int* mask = nullptr;
     TILE_PROLOGUE();
     double* g = grad_tab[s.inst] + (long long)s.j * 2 * s.N;
+    auto put = [&](long long il, zd Kz, zd Tz) {
+        const zd gv = 2.0 * gop(Kz, Tz);
+        g[il] = gv.x;
+        g[s.N + il] = gv.y;
+    };
+    if constexpr (DIM == 3) {
+        const int y = tile.y0 + ty;
+        const double m0 = s.h / 6.0, m1 = 4.0 * s.h / 6.0, ih = 1.0 / s.h;
+        __shared__ zd buf[2][1][kPP];
+        zmarch_lds<TY / 4, 1, true, true, double, double>(
+            s, tile, (int)(threadIdx.x & 63), ty, buf, m0, m1, ih, [&](int, long long i) { return zeta[s.off + i]; },
+            [&](int z, const auto& P) {
+                if (x >= s.nx || y >= s.ny || z >= s.nz) return;
+                zd Mz, Kz, Tz;
+                zcombine<true, true, double>(P[0][0], P[0][1], P[0][2], m0, m1, ih, s.kv[0], s.kv[1], s.kv[2], Mz, Kz,
+                                             Tz);
+                put(((long long)z * s.ny + y) * s.nx + x, Kz, Tz);
+            });
+    } else {
+        FOR_ROWS(TY) {
+            Nbr<DIM> n;
+            make_nbr<DIM>(s, x, y, pz, n);
+            zd Mz, Kz, Tz;
+            stencil<DIM, true, true, double>(
+                [&](int a, int b, int c) { return zeta[s.off + nb_index<DIM>(n, a, b, c)]; }, s.h, s.kv[0], s.kv[1],
+                s.kv[2], Mz, Kz, Tz);
+            put(nb_index<DIM>(n, 1, 1, 1), Kz, Tz);
+        }
+    }
+}
+
+template <int DIM, int TY, int JM>
+__global__ __launch_bounds__(kBlock) void k_energy_grad_nodal(const Sys* sys, const Tile* tiles, const Terms T,
+                                                             const zd* eta, double* const* grad_tab, double* part,
+                                                             int ntiles) {
+    __shared__ double lds[4];
+    const int* mask = nullptr;
+    TILE_PROLOGUE();
+    double* g = grad_tab[s.inst];
+    const long long o0 = s.off - (long long)s.j * s.N;     // amplitude 0 of the instance
     double acc[1] = {0.0};
     FOR_ROWS(TY) {
-        Nbr<DIM> n;
-        make_nbr<DIM>(s, x, y, pz, n);
-        zd Mz, Kz, Tz;
-        stencil<DIM, true, true, double>([&](int a, int b, int c) { return zeta[s.off + nb_index<DIM>(n, a, b, c)]; },
-                                         s.h, s.kv[0], s.kv[1], s.kv[2], Mz, Kz, Tz);
-        const long long il = nb_index<DIM>(n, 1, 1, 1);
-        const long long i0 = s.off - (long long)s.j * s.N;     // amplitude 0 of this instance
-        zd e[kMaxJ], h[kMaxJ];
+        if (rr_ % T.J != s.j) continue;
+        const long long i = ((long long)pz * s.ny + y) * s.nx + x;
+        zd e[JM], h[JM];
         double A = 0.0;
-        for (int l = 0; l < T.J; ++l) {
-            e[l] = eta[i0 + l * s.N + il];
+#pragma unroll
+        for (int l = 0; l < JM; ++l) {
+            e[l] = l < T.J ? eta[o0 + l * s.N + i] : zd{0.0, 0.0};
             A += abs2(e[l]);
         }
         double d;
-        bulk_h(T, s, e, d, h);
-        const zd F = d * e[s.j] + h[s.j];
-        const zd gv = 2.0 * (s.w * F + gop(Kz, Tz));
-        g[il] = gv.x;
-        g[s.N + il] = gv.y;
-        if (s.j == 0) acc[0] += s.w * 2.0 * A / (2.0 * s.a0);
+        bulk_h_reg<JM>(T, s, e, d, h);
+#pragma unroll
+        for (int l = 0; l < JM; ++l) {
+            if (l >= T.J) break;
+            const zd F = d * e[l] + h[l];
+            const long long q = (long long)l * 2 * s.N + i;
+            g[q] += 2.0 * s.w * F.x;
+            g[s.N + q] += 2.0 * s.w * F.y;
+        }
+        acc[0] += s.w * 2.0 * A / (2.0 * s.a0);
     }
     block_sum<1>(acc, lds);
     if (threadIdx.x == 0) part[kE1 * (long long)ntiles + blockIdx.x] = acc[0];
@@ -1834,19 +1870,6 @@ template void launch_precond_mg<double>(const Dev&, const MgLevels&, const zd*, 
 template void launch_precond_mg<float>(const Dev&, const MgLevels&, const zf*, zf*, zf*, zf*, zf*, zf*, zf*, zf*, int,
                                        int, const int*, hipStream_t);
 
-void launch_mass_solve(const Dev& d, const zd* eta, zd* zeta, zd* r, zd* p0, zd* p1, zd* q, double* part, int iters,
-                       hipStream_t st) {
-    // zeta = M^{-1} G eta by Chebyshev-Jacobi iterations with the exact bounds of D^{-1} M
-    // ([1/2, 3/2]^dim): the error contracts by (sqrt(3^dim) - 1)/(sqrt(3^dim) + 1) per iteration.
-    (void)q;
-    (void)part;
-    dispatch(d, [&](auto D, auto TY) {
-        constexpr int DIM = D(), TYv = TY();
-        cb_init_launch<DIM, TYv, double, 3>(d, nullptr, nullptr, eta, r, p0, zeta, st);
-        cb_iterations<DIM, TYv, double, 0>(d, iters, p0, p1, r, zeta, nullptr, st);
-    });
-}
-
 void launch_reduce(const Dev& d, const double* part, int slot0, int nvals, bool chunk_ranges, double* out, int ld,
                    const int* mask, hipStream_t st) {
     ProbeScope ps(d, KID_REDUCE, st);
@@ -1920,14 +1943,20 @@ void launch_solve_y(const Dev& d, const Krylov& kr, hipStream_t st) {
 
 void launch_energy_parts(const Dev& d, const zd* eta, const zd* zeta, double* part, hipStream_t st) {
     dispatch(d, [&](auto D, auto TY) {
-        hipLaunchKernelGGL((k_energy<D(), TY()>), TILE_GRID, d.sys, d.tiles, d.terms, eta, zeta, part, d.ntiles);
+        dispatch_jm(d.J, [&](auto JM) {
+            hipLaunchKernelGGL((k_energy<D(), TY(), JM()>), TILE_GRID, d.sys, d.tiles, d.terms, eta, zeta, part,
+                               d.ntiles);
+        });
     });
 }
 void launch_energy_grad(const Dev& d, const zd* eta, const zd* zeta, double* const* grad_tab, double* part,
                         hipStream_t st) {
     dispatch(d, [&](auto D, auto TY) {
-        hipLaunchKernelGGL((k_energy_grad<D(), TY()>), TILE_GRID, d.sys, d.tiles, d.terms, eta, zeta, grad_tab, part,
-                           d.ntiles);
+        hipLaunchKernelGGL((k_energy_grad<D(), TY()>), TILE_GRID, d.sys, d.tiles, zeta, grad_tab);
+        dispatch_jm(d.J, [&](auto JM) {
+            hipLaunchKernelGGL((k_energy_grad_nodal<D(), TY(), JM()>), TILE_GRID, d.sys, d.tiles, d.terms, eta,
+                               grad_tab, part, d.ntiles);
+        });
     });
 }
 void launch_rotation(const Dev& d, const zd* eta, double* const* omega_tab, double* const* h_tab, const RefineArgs& ra,

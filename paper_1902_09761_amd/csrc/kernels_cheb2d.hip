@@ -30,25 +30,6 @@ __device__ __forceinline__ int wrapi(int g, int n) {
     return g < 0 ? g + n : g;
 }
 
-// Whole-wave lane shifts by one lane (DPP wave_shr:1 / wave_shl:1): after lane_shift<kDppWaveShr1>, lane i
-// holds lane i - 1's value (lane 0 gets 0); after kDppWaveShl1, lane i + 1's (lane 63 gets 0).
-constexpr int kDppWaveShl1 = 0x130, kDppWaveShr1 = 0x138;
-template <int CTRL>
-__device__ __forceinline__ float lane_shift(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-template <int CTRL>
-__device__ __forceinline__ double lane_shift(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffLL), CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-template <int CTRL, typename T>
-__device__ __forceinline__ cx<T> lane_shift(cx<T> v) {
-    return cx<T>{lane_shift<CTRL>(v.x), lane_shift<CTRL>(v.y)};
-}
-
 // The operators of the inner solves in split form.  With P = [1 4 1], Q = [-1 2 -1] = 6 delta - P and
 // E = [-1 0 1], the bilinear element stencils are M = (h/6)^2 P(x)P,
 // K = (1/6)(Q(x)P + P(x)Q) = (delta(x)P + P(x)delta) - P(x)P/3 and T_j = (h/6)(k0 E(x)P + k1 P(x)E).

@@ -1,6 +1,9 @@
-// Step 1 of the block preconditioner (Eq. (12), the mass solve M x1 = beta1) by a separable approximate
-// inverse of the mass matrix, for gfx950, with its launcher.
+// The mass matrix's inverse on the uniform periodic mesh, for gfx950: step 1 of the block preconditioner
+// (Eq. (12), M x1 = beta1) by a separable approximate inverse, and the auxiliary field zeta = M^{-1} G eta to
+// FP64 rounding by one line filter per direction, with their launchers.
 #include "kernels_common.h"
+
+#include <algorithm>
 
 namespace apfc {
 
@@ -127,5 +130,199 @@ void launch_mass_sep(const Dev& d, int R, const cx<T>* v, cx<T>* x1, const int* 
 }
 template void launch_mass_sep<double>(const Dev&, int, const zd*, zd*, const int*, hipStream_t);
 template void launch_mass_sep<float>(const Dev&, int, const zf*, zf*, const int*, hipStream_t);
+
+// ------------------------------------------------------------------------------------------
+// zeta_j = M^{-1} G_j eta_j (the auxiliary field of Algorithm 1, the energy and its gradient) to FP64 rounding.
+//
+// With the 1D matrices m = (h/6) P, P = [1 4 1], k = (1/h) Q, Q = [-1 2 -1], d = E/2, E = [-1 0 1] of the
+// directions, M = m (x) m (x) m, so M^{-1} G_j = sum_dir P_dir^{-1} (-(6/h^2) Q_dir + i (6 k_{j,dir}/h) E_dir):
+// the other directions' mass factors cancel, and zeta is the sum of one line filter per direction.  P^{-1} on
+// a line has the entries rho^|n|/(2 sqrt 3), rho = sqrt 3 - 2; with |rho|^kLineHalo < 1e-17 the line solve is
+// a causal and an anticausal first-order recursion c+_i = y_i + rho c+_{i-1}, c-_i = y_i + rho c-_{i+1},
+// P^{-1} y = (c+ + c- - y)/(2 sqrt 3), each started kLineHalo nodes before its first output (periodic
+// images of a short line included).  Bound by memory: three (2D: two) passes over eta and zeta.  Solving for
+// M by 100 (2D: 60) Chebyshev iterations to the same error, a launch and six vectors each, took apfc_energy of
+// 1024^2 x 3 to 2736 us (145 us with the filters) and, with the nodal part of the gradient formed once per
+// amplitude, apfc_energy_grad of 90 x 96 x 77 x 6 to 7618 us (358 us).
+// ------------------------------------------------------------------------------------------
+constexpr int kLineHalo = 32;
+constexpr double kRho = -0.26794919243112270647;        // sqrt(3) - 2
+constexpr double kLineNorm = 0.28867513459481288225;    // 1/(2 sqrt 3)
+
+// x: a wave holds 64 blocks of 8 consecutive nodes, whole line segments (output nodes plus kLineHalo on either
+// side) packed one after the other (gpw of them per wave, so that short lines leave few lanes idle).  A lane
+// runs both recursions over its block and takes the rest of the recursion from the four neighbouring lanes'
+// block sums (rho^32 of anything further away is below rounding); global loads and stores are coalesced
+// through LDS (blocks padded by one node against bank conflicts).
+constexpr int kLineB = 8, kLineMax = 64 * kLineB - 2 * kLineHalo;
+
+__device__ __forceinline__ int line_segs(int n) { return (n + kLineMax - 1) / kLineMax; }
+
+__global__ __launch_bounds__(kBlock) void k_zeta_x(const Sys* sys, const zd* __restrict__ eta, zd* __restrict__ zeta) {
+    __shared__ zd buf[kBlock / 64][64 * (kLineB + 1)];
+    const Sys* s = sys + blockIdx.y;
+    const int nx = s->nx, segs = line_segs(nx), nout = (nx + segs - 1) / segs;
+    const int gw = (nout + 2 * kLineHalo + kLineB - 1) / kLineB, gpw = 64 / gw, gn = gw * kLineB;
+    const long long off = s->off, items = (long long)s->ny * s->nz * segs;
+    const int wv = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    const double a = -6.0 / (s->h * s->h) * kLineNorm, b = 6.0 * s->kv[0] / s->h * kLineNorm;
+    auto slot = [](int e) { return e + e / kLineB; };
+    zd* w = buf[wv];
+    // no neighbour inside the segment: the block's own end stands in, kLineHalo nodes from any output
+    const bool first = lane % gw == 0, last = lane % gw == gw - 1 || lane == 63;
+    const double rb = kRho * kRho, rho8 = rb * rb * rb * rb;
+    for (long long it0 = (long long)blockIdx.x * 4 * gpw; it0 < items; it0 += (long long)gridDim.x * 4 * gpw) {
+        auto node = [&](int e, bool& out) -> long long {   // node of element e, -1: none; out: an output node
+            const int g = e / gn, p = e - g * gn;
+            const long long item = it0 + (long long)wv * gpw + g;
+            out = false;
+            if (g >= gpw || item >= items) return -1;
+            const long long row = item / segs;
+            const int xs = (int)(item - row * segs) * nout;
+            int x = (xs - kLineHalo + p) % nx;
+            x = x < 0 ? x + nx : x;
+            out = p >= kLineHalo && p < kLineHalo + nout && xs - kLineHalo + p < nx;
+            return off + row * nx + x;
+        };
+        bool out[kLineB];
+        long long idx[kLineB];
+#pragma unroll
+        for (int i = 0; i < kLineB; ++i) {
+            const int e = i * 64 + lane;
+            idx[i] = node(e, out[i]);
+            w[slot(e)] = idx[i] >= 0 ? eta[idx[i]] : zd{0.0, 0.0};
+        }
+        __syncthreads();
+        zd u[kLineB + 2];
+        u[0] = w[slot(first ? lane * kLineB : lane * kLineB - 1)];
+#pragma unroll
+        for (int k = 0; k < kLineB; ++k) u[k + 1] = w[slot(lane * kLineB + k)];
+        u[kLineB + 1] = w[slot(last ? lane * kLineB + kLineB - 1 : (lane + 1) * kLineB)];
+        zd y[kLineB], f[kLineB], c[kLineB];
+#pragma unroll
+        for (int k = 0; k < kLineB; ++k)
+            y[k] = a * ((u[k + 1] + u[k + 1]) - (u[k] + u[k + 2])) + b * mul_i(u[k + 2] - u[k]);
+        f[0] = y[0];
+        c[kLineB - 1] = y[kLineB - 1];
+#pragma unroll
+        for (int k = 1; k < kLineB; ++k) {
+            f[k] = y[k] + kRho * f[k - 1];
+            c[kLineB - 1 - k] = y[kLineB - 1 - k] + kRho * c[kLineB - k];
+        }
+        zd cf{0.0, 0.0}, cb{0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            cf = lane_shift<kDppWaveShr1>(f[kLineB - 1] + rho8 * cf);
+            cb = lane_shift<kDppWaveShl1>(c[0] + rho8 * cb);
+        }
+        double pw[kLineB + 1];
+        pw[0] = 1.0;
+#pragma unroll
+        for (int k = 1; k <= kLineB; ++k) pw[k] = pw[k - 1] * kRho;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kLineB; ++k)
+            w[slot(lane * kLineB + k)] = ((f[k] + pw[k + 1] * cf) + (c[k] + pw[kLineB - k] * cb)) - y[k];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kLineB; ++i)
+            if (out[i]) zeta[idx[i]] = w[slot(i * 64 + lane)];
+        __syncthreads();
+    }
+}
+
+// y (DIR = 1) and z (DIR = 2), zeta += the direction's filter of eta: a thread takes kLineSeg consecutive nodes of
+// one line, lanes along x.  It walks down to them from kLineHalo nodes before, keeping c+ of its outputs in
+// registers, and back up from kLineHalo nodes after; the re-read nodes come from L2.
+constexpr int kLineSeg = 32;
+
+template <int DIR>
+__global__ __launch_bounds__(kBlock) void k_zeta_line(const Sys* sys, const zd* __restrict__ eta, zd* __restrict__ zeta) {
+    const Sys* s = sys + blockIdx.y;
+    const int n = DIR == 1 ? s->ny : s->nz, nx = s->nx;
+    const int lines = DIR == 1 ? nx * s->nz : nx * s->ny, segs = (n + kLineSeg - 1) / kLineSeg;
+    const long long t = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (t >= (long long)lines * segs) return;
+    const int seg = (int)(t / lines), line = (int)(t - (long long)seg * lines);
+    const long long stride = DIR == 1 ? nx : (long long)nx * s->ny;
+    const long long base = s->off + (DIR == 1 ? (long long)(line / nx) * nx * s->ny + line % nx : (long long)line);
+    const double a = -6.0 / (s->h * s->h) * kLineNorm, b = 6.0 * s->kv[DIR] / s->h * kLineNorm;
+    const zd* e = eta + base;
+    zd* z = zeta + base;
+    auto wrap = [&](int p) {
+        p %= n;
+        return p < 0 ? p + n : p;
+    };
+    auto src = [&](zd l, zd c, zd r) { return a * ((c + c) - (l + r)) + b * mul_i(r - l); };
+    const int s0 = seg * kLineSeg;
+    zd f[kLineSeg], v{0.0, 0.0};
+    {
+        int p = wrap(s0 - kLineHalo - 1);
+        auto next = [&]() {
+            const zd u = e[p * stride];
+            p = p + 1 == n ? 0 : p + 1;
+            return u;
+        };
+        zd l = next(), c = next();
+#pragma unroll 8
+        for (int k = 0; k < kLineHalo; ++k) {
+            const zd r = next();
+            v = src(l, c, r) + kRho * v;
+            l = c;
+            c = r;
+        }
+#pragma unroll
+        for (int k = 0; k < kLineSeg; ++k) {
+            const zd r = next();
+            v = src(l, c, r) + kRho * v;
+            f[k] = v;
+            l = c;
+            c = r;
+        }
+    }
+    v = zd{0.0, 0.0};
+    int p = wrap(s0 + kLineSeg + kLineHalo);
+    auto prev = [&]() {
+        const zd u = e[p * stride];
+        p = p == 0 ? n - 1 : p - 1;
+        return u;
+    };
+    zd r = prev(), c = prev();
+#pragma unroll 8
+    for (int k = 0; k < kLineHalo; ++k) {
+        const zd l = prev();
+        v = src(l, c, r) + kRho * v;
+        r = c;
+        c = l;
+    }
+#pragma unroll
+    for (int k = kLineSeg - 1; k >= 0; --k) {
+        const zd l = prev();
+        const zd y = src(l, c, r);
+        v = y + kRho * v;
+        if (s0 + k < n) {
+            const long long o = (s0 + k) * stride;
+            z[o] = z[o] + ((f[k] + v) - y);
+        }
+        r = c;
+        c = l;
+    }
+}
+
+void launch_zeta(const Dev& d, const zd* eta, zd* zeta, hipStream_t st) {
+    const int* mx = d.maxn;
+    auto blocks = [](long long threads) { return (unsigned)((threads + kBlock - 1) / kBlock); };
+    const int segs = (mx[0] + kLineMax - 1) / kLineMax, nout = (mx[0] + segs - 1) / segs;
+    const int gpw = 64 / ((nout + 2 * kLineHalo + kLineB - 1) / kLineB);
+    const long long rows = (long long)mx[1] * mx[2] * segs;
+    hipLaunchKernelGGL(k_zeta_x, dim3((unsigned)std::min<long long>((rows + 4 * gpw - 1) / (4 * gpw), 1 << 20), d.S),
+                       dim3(kBlock), 0, st, d.sys, eta, zeta);
+    auto segn = [](int n) { return (long long)(n + kLineSeg - 1) / kLineSeg; };
+    hipLaunchKernelGGL(k_zeta_line<1>, dim3(blocks((long long)mx[0] * mx[2] * segn(mx[1])), d.S), dim3(kBlock), 0, st,
+                       d.sys, eta, zeta);
+    if (d.dim == 3)
+        hipLaunchKernelGGL(k_zeta_line<2>, dim3(blocks((long long)mx[0] * mx[1] * segn(mx[2])), d.S), dim3(kBlock), 0,
+                           st, d.sys, eta, zeta);
+}
 
 }  // namespace apfc
