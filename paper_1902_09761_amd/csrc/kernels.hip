@@ -962,15 +962,23 @@ __device__ void stage_rotations(const Krylov& kr, int si, int k, double* rot) {
     __syncthreads();
 }
 
-// The nvals sums of a pass over partials part[v * P + t], t in [beg, end), in a fixed order (one wave per
-// value), into LDS out (whole workgroup).
+// The nvals sums of a pass over partials part[v * P + t], t in [beg, end), in a fixed order, into LDS out
+// (whole workgroup).  A wave takes up to PV of its values at a time, so their loads are in flight together: one
+// value after the other, the 61 sums of a 30-vector pass took 16 load latencies per wave.
 __device__ void pass_sums(const double* part, long long P, int beg, int end, int nvals, double* out) {
+    constexpr int PV = 8;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = (int)blockDim.x >> 6;
-    for (int v = wv; v < nvals; v += nw) {
-        double a = 0.0;
-        for (int t = beg + lane; t < end; t += 64) a += part[v * P + t];
-        a = wave_sum(a);
-        if (lane == 0) out[v] = a;
+    for (int v0 = wv; v0 < nvals; v0 += nw * PV) {
+        double a[PV];
+#pragma unroll
+        for (int u = 0; u < PV; ++u) a[u] = 0.0;
+        for (int t = beg + lane; t < end; t += 64)
+#pragma unroll
+            for (int u = 0; u < PV; ++u)
+                if (v0 + u * nw < nvals) a[u] += part[(v0 + u * nw) * P + t];
+        wave_sums<PV>(a, [&](int u, double s) {
+            if (v0 + u * nw < nvals) out[v0 + u * nw] = s;
+        });
     }
     __syncthreads();
 }
@@ -1047,16 +1055,12 @@ __global__ __launch_bounds__(kBlock) void k_gs(const Sys* sys, const Chunk* chun
             }
             acc[2 * NV] += abs2(wv);
         }
-        block_sum<2 * NV + 1>(acc, lds);
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int l = 0; l < NV; ++l)
-                if (l < nv) {
-                    part2[(2 * l) * (long long)nchunks + ci] = acc[2 * l];
-                    part2[(2 * l + 1) * (long long)nchunks + ci] = acc[2 * l + 1];
-                }
-            part2[(2 * nv) * (long long)nchunks + ci] = acc[2 * NV];
-        }
+        block_totals<2 * NV + 1>(acc, lds, [&](int i, double t) {
+            if (i == 2 * NV)
+                part2[(2 * nv) * (long long)nchunks + ci] = t;
+            else if (i < 2 * nv)
+                part2[i * (long long)nchunks + ci] = t;
+        });
         if (last_of_system(kr.tick_c, si, s.cend - s.cbeg, &flag)) {
             pass_sums(part2, nchunks, s.cbeg, s.cend, nvals, hh[1]);
             stage_rotations(kr, si, k, rot);
@@ -1065,26 +1069,44 @@ __global__ __launch_bounds__(kBlock) void k_gs(const Sys* sys, const Chunk* chun
     }
 }
 
-__global__ void k_solve_y(Krylov kr, int S) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S || !kr.solve_active[s]) return;
+// Back substitution H y = g of the cycle's kc columns, one wave per system: the wave stages the triangle in
+// LDS, one thread walks it (row by row, columns in ascending order).  Walking H in memory took 73 us for 30
+// columns, one load latency per element.
+__global__ __launch_bounds__(64) void k_solve_y(Krylov kr) {
+    __shared__ zd H[kMaxRestart][kMaxRestart + 1], g[kMaxRestart], y[kMaxRestart];
+    const int s = blockIdx.x, lane = threadIdx.x;
+    if (!kr.solve_active[s]) return;
     const int kc = kr.kcount[s], m = kr.m;
     if (kc <= 0) return;
-    const double* g = kr.g + (long long)s * 2 * (m + 1);
-    double* y = kr.y + (long long)s * 2 * m;
-    for (int i = kc - 1; i >= 0; --i) {
-        double tr = g[2 * i], ti = g[2 * i + 1];
-        for (int l = i + 1; l < kc; ++l) {
-            const double* col = kr.H + ((long long)s * m + l) * 2 * (m + 1);
-            const double hr = col[2 * i], hi = col[2 * i + 1];
-            tr -= hr * y[2 * l] - hi * y[2 * l + 1];
-            ti -= hr * y[2 * l + 1] + hi * y[2 * l];
+#pragma unroll 8
+    for (int l = 0; l < kc; ++l) {
+        const double* c = kr.H + ((long long)s * m + l) * 2 * (m + 1);
+        if (lane <= l) H[lane][l] = zd{c[2 * lane], c[2 * lane + 1]};
+    }
+    if (lane < kc) {
+        const double* gs = kr.g + (long long)s * 2 * (m + 1);
+        g[lane] = zd{gs[2 * lane], gs[2 * lane + 1]};
+    }
+    __syncthreads();
+    if (lane == 0)
+        for (int i = kc - 1; i >= 0; --i) {
+            double tr = g[i].x, ti = g[i].y;
+#pragma unroll 8
+            for (int l = i + 1; l < kc; ++l) {
+                const double hr = H[i][l].x, hi = H[i][l].y;
+                tr -= hr * y[l].x - hi * y[l].y;
+                ti -= hr * y[l].y + hi * y[l].x;
+            }
+            const double dr = H[i][i].x, di = H[i][i].y;
+            const double den = dr * dr + di * di;
+            y[i].x = den > 0.0 ? (tr * dr + ti * di) / den : 0.0;
+            y[i].y = den > 0.0 ? (ti * dr - tr * di) / den : 0.0;
         }
-        const double* cc = kr.H + ((long long)s * m + i) * 2 * (m + 1);
-        const double dr = cc[2 * i], di = cc[2 * i + 1];
-        const double den = dr * dr + di * di;
-        y[2 * i] = den > 0.0 ? (tr * dr + ti * di) / den : 0.0;
-        y[2 * i + 1] = den > 0.0 ? (ti * dr - tr * di) / den : 0.0;
+    __syncthreads();
+    if (lane < kc) {
+        double* out = kr.y + (long long)s * 2 * m;
+        out[2 * lane] = y[lane].x;
+        out[2 * lane + 1] = y[lane].y;
     }
 }
 
@@ -1938,7 +1960,7 @@ void launch_cycle_start(const Dev& d, const Krylov& kr, const double* part, bool
 }
 void launch_solve_y(const Dev& d, const Krylov& kr, hipStream_t st) {
     ProbeScope ps(d, KID_SMALL, st);
-    hipLaunchKernelGGL(k_solve_y, dim3((d.S + 63) / 64), dim3(64), 0, st, kr, d.S);
+    hipLaunchKernelGGL(k_solve_y, dim3(d.S), dim3(64), 0, st, kr);
 }
 
 void launch_energy_parts(const Dev& d, const zd* eta, const zd* zeta, double* part, hipStream_t st) {

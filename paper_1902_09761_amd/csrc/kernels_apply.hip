@@ -97,8 +97,22 @@ __device__ __forceinline__ void colmarch_A(const Sys& s, int x, int y0, const LO
 // W = A Z at every node and, fused, the first Gram-Schmidt pass: per-tile partials of V_i^H w
 // (i < nv) and of |w|^2 (slots 2i, 2i+1 and 2 nv of part, stride ntiles).  2D: column-marching
 // tiles (TY/4 rows per thread); 3D: k_apply_dot3d below.
-// NV >= nv basis vectors; with NV <= 8 the launch uses NV = nv exactly, so the basis loads carry no test.
-template <int TY, typename T, int NV>
+// Up to kDotVecs basis vectors: NV = nv, so the basis loads carry no test.  More (GROUPS): blockIdx.y takes
+// kDotVecs of them each and forms its own w (z comes from L2 then), the first group stores w.  One workgroup
+// with 2 nv + 1 accumulators for up to 32 vectors had 134 registers of them and up to 256 loads per thread
+// one after the other: 36 us at 64^2 x 3 and 52 us at 256^2 x 3 (FP64, 17 to 30 vectors).
+constexpr int kDotVecs = 8;
+// value i of the kernel's 2 NV + 1 sums (2 l, 2 l + 1: vector l; 2 NV: |w|^2) into the tile's partials
+template <int NV, bool GROUPS>
+__device__ __forceinline__ void dot_part(int i, double t, int nv, double* part, int ntiles) {
+    const int first = GROUPS ? (int)blockIdx.y * kDotVecs : 0;
+    if (i == 2 * NV) {
+        if (first == 0) part[(2 * nv) * (long long)ntiles + blockIdx.x] = t;
+    } else if (2 * first + i < 2 * nv) {
+        part[(2 * first + i) * (long long)ntiles + blockIdx.x] = t;
+    }
+}
+template <int TY, typename T, int NV, bool GROUPS>
 __global__ __launch_bounds__(kBlock) void k_apply_dot2d(const Sys* sys, const Tile* tiles, const int* mask,
                                                        const cx<T>* __restrict__ Z, const double* __restrict__ dnode,
                                                        cx<T>* __restrict__ W, const cx<T>* __restrict__ V,
@@ -113,19 +127,23 @@ __global__ __launch_bounds__(kBlock) void k_apply_dot2d(const Sys* sys, const Ti
     for (int i = 0; i < 2 * NV + 1; ++i) acc[i] = 0.0;
     const cx<T>* zz = Z + s.off;
     const cx<T>* ze = Z + NT + s.off;
+    const cx<T>* Vg = GROUPS ? V + (long long)blockIdx.y * kDotVecs * vstride : V;
+    const int nvg = GROUPS ? nv - (int)blockIdx.y * kDotVecs : nv;
     auto load = [&](int f, long long i) { return ld<double>(f == 0 ? zz : ze, i); };
     auto emit = [&](long long il, const zd& a1, const zd& a2) {
         // w is stored in the basis precision; the first pass takes the stored (rounded) w, so that the
         // projection of k_proj_final and the coefficients belong to the same vector
         const zd y1 = rounded<T>(a1), y2 = rounded<T>(a2);
-        stv(W, s.off + il, y1);
-        stv(W, NT + s.off + il, y2);
+        if (!GROUPS || blockIdx.y == 0) {
+            stv(W, s.off + il, y1);
+            stv(W, NT + s.off + il, y2);
+        }
         acc[2 * NV] += abs2(y1) + abs2(y2);
 #pragma unroll
         for (int l = 0; l < NV; ++l)
-            if (NV <= 8 || l < nv) {
-                const zd p = cdot(ld<double>(V, l * vstride + s.off + il), y1),
-                         q = cdot(ld<double>(V, l * vstride + NT + s.off + il), y2);
+            if (!GROUPS || l < nvg) {
+                const zd p = cdot(ld<double>(Vg, l * vstride + s.off + il), y1),
+                         q = cdot(ld<double>(Vg, l * vstride + NT + s.off + il), y2);
                 acc[2 * l] += p.x + q.x;
                 acc[2 * l + 1] += p.y + q.y;
             }
@@ -134,16 +152,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_dot2d(const Sys* sys, const Ti
         colmarch_A<RR, false>(s, x, y0, load, dnode, emit);
     else
         colmarch_A<RR, true>(s, x, y0, load, dnode, emit);
-    block_sum<2 * NV + 1>(acc, lds);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int l = 0; l < NV; ++l)
-            if (l < nv) {
-                part[(2 * l) * (long long)ntiles + blockIdx.x] = acc[2 * l];
-                part[(2 * l + 1) * (long long)ntiles + blockIdx.x] = acc[2 * l + 1];
-            }
-        part[(2 * nv) * (long long)ntiles + blockIdx.x] = acc[2 * NV];
-    }
+    block_totals<2 * NV + 1>(acc, lds, [&](int i, double t) { dot_part<NV, GROUPS>(i, t, nv, part, ntiles); });
 }
 
 // R = B - A X and per-tile partials of |R|^2, |B|^2 (slots kRR, kBB), on column-marching tiles.
@@ -188,7 +197,7 @@ __global__ __launch_bounds__(kBlock) void k_residual2d(const Sys* sys, const Til
     const int xc = x < s.nx ? x : s.nx - 1, yc = y < s.ny ? y : s.ny - 1;    \
     const double m0 = s.h * (1.0 / 6.0), m1 = s.h * (4.0 / 6.0), ih = 1.0 / s.h;
 
-template <int TY, typename T, int NV>
+template <int TY, typename T, int NV, bool GROUPS>
 __global__ __launch_bounds__(kBlock) void k_apply_dot3d(const Sys* sys, const Tile* tiles, const int* mask,
                                                        const cx<T>* Z, const double* dnode, cx<T>* W, const cx<T>* V,
                                                        long long vstride, int nv, double* part, long long NT,
@@ -197,6 +206,8 @@ __global__ __launch_bounds__(kBlock) void k_apply_dot3d(const Sys* sys, const Ti
     BRICK_PROLOGUE();
     const cx<T>* zz = Z + s.off;
     const cx<T>* ze = Z + NT + s.off;
+    const cx<T>* Vg = GROUPS ? V + (long long)blockIdx.y * kDotVecs * vstride : V;
+    const int nvg = GROUPS ? nv - (int)blockIdx.y * kDotVecs : nv;
     double acc[2 * NV + 1];
 #pragma unroll
     for (int i = 0; i < 2 * NV + 1; ++i) acc[i] = 0.0;
@@ -206,14 +217,16 @@ __global__ __launch_bounds__(kBlock) void k_apply_dot3d(const Sys* sys, const Ti
         zd a1, a2;
         apply_A_planes(s, P, m0, m1, ih, dnode[s.doff + il], a1, a2);
         const zd y1 = rounded<T>(a1), y2 = rounded<T>(a2);
-        stv(W, s.off + il, y1);
-        stv(W, NT + s.off + il, y2);
+        if (!GROUPS || blockIdx.y == 0) {
+            stv(W, s.off + il, y1);
+            stv(W, NT + s.off + il, y2);
+        }
         acc[2 * NV] += abs2(y1) + abs2(y2);
 #pragma unroll
         for (int l = 0; l < NV; ++l)
-            if (NV <= 8 || l < nv) {
-                const zd p = cdot(ld<double>(V, l * vstride + s.off + il), y1),
-                     q = cdot(ld<double>(V, l * vstride + NT + s.off + il), y2);
+            if (!GROUPS || l < nvg) {
+                const zd p = cdot(ld<double>(Vg, l * vstride + s.off + il), y1),
+                     q = cdot(ld<double>(Vg, l * vstride + NT + s.off + il), y2);
                 acc[2 * l] += p.x + q.x;
                 acc[2 * l + 1] += p.y + q.y;
             }
@@ -226,16 +239,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_dot3d(const Sys* sys, const Ti
     else
         zmarch<TY / 4, 2, true, true, double>(
             s, xc, yc, tile.z, m0, m1, ih, [&](int f, long long i) { return ld<double>(f == 0 ? zz : ze, i); }, emit);
-    block_sum<2 * NV + 1>(acc, lds);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int l = 0; l < NV; ++l)
-            if (l < nv) {
-                part[(2 * l) * (long long)ntiles + blockIdx.x] = acc[2 * l];
-                part[(2 * l + 1) * (long long)ntiles + blockIdx.x] = acc[2 * l + 1];
-            }
-        part[(2 * nv) * (long long)ntiles + blockIdx.x] = acc[2 * NV];
-    }
+    block_totals<2 * NV + 1>(acc, lds, [&](int i, double t) { dot_part<NV, GROUPS>(i, t, nv, part, ntiles); });
 }
 
 template <int TY, typename RT>
@@ -302,27 +306,28 @@ void launch_apply_dot(const Dev& d, const cx<T>* Z, const double* dnode, cx<T>* 
     // reads z, d, nv basis vectors (stored like z); writes w (stored like z)
     ProbeScope ps(d, KID_APPLY, st, (double)d.NT * (2.0 * sizeof(cx<T>) * (2 + nv) + 8.0 / d.J), mask, true);
     dispatch(d, [&](auto D, auto TY) {
-        auto go = [&](auto nvc) {
+        auto go = [&](auto nvc, auto groups) {
+            const dim3 g(d.ntiles, decltype(groups)::value ? (nv + kDotVecs - 1) / kDotVecs : 1);
             if constexpr (D() == 2)
-                ps.launch(k_apply_dot2d<TY(), T, decltype(nvc)::value>, dim3(d.ntiles), dim3(kBlock), d.sys, d.tiles,
-                          mask, Z, dnode, W, V, vstride, nv, part, d.NT, d.ntiles);
+                ps.launch(k_apply_dot2d<TY(), T, decltype(nvc)::value, decltype(groups)::value>, g, dim3(kBlock), d.sys,
+                          d.tiles, mask, Z, dnode, W, V, vstride, nv, part, d.NT, d.ntiles);
             else
-                ps.launch(k_apply_dot3d<TY(), T, decltype(nvc)::value>, dim3(d.ntiles), dim3(kBlock), d.sys, d.tiles,
-                          mask, Z, dnode, W, V, vstride, nv, part, d.NT, d.ntiles);
+                ps.launch(k_apply_dot3d<TY(), T, decltype(nvc)::value, decltype(groups)::value>, g, dim3(kBlock), d.sys,
+                          d.tiles, mask, Z, dnode, W, V, vstride, nv, part, d.NT, d.ntiles);
         };
+        static_assert(kDotVecs == 8, "one case per vector count");
+        const std::false_type one{};
         switch (nv) {
-            case 1: go(std::integral_constant<int, 1>{}); return;
-            case 2: go(std::integral_constant<int, 2>{}); return;
-            case 3: go(std::integral_constant<int, 3>{}); return;
-            case 4: go(std::integral_constant<int, 4>{}); return;
-            case 5: go(std::integral_constant<int, 5>{}); return;
-            case 6: go(std::integral_constant<int, 6>{}); return;
-            case 7: go(std::integral_constant<int, 7>{}); return;
-            case 8: go(std::integral_constant<int, 8>{}); return;
-            default: break;
+            case 1: go(std::integral_constant<int, 1>{}, one); break;
+            case 2: go(std::integral_constant<int, 2>{}, one); break;
+            case 3: go(std::integral_constant<int, 3>{}, one); break;
+            case 4: go(std::integral_constant<int, 4>{}, one); break;
+            case 5: go(std::integral_constant<int, 5>{}, one); break;
+            case 6: go(std::integral_constant<int, 6>{}, one); break;
+            case 7: go(std::integral_constant<int, 7>{}, one); break;
+            case 8: go(std::integral_constant<int, 8>{}, one); break;
+            default: go(std::integral_constant<int, kDotVecs>{}, std::true_type{}); break;
         }
-        if (nv <= 16) go(std::integral_constant<int, 16>{});
-        else go(std::integral_constant<int, 32>{});
     });
 }
 template void launch_apply_dot<double>(const Dev&, const zd*, const double*, zd*, const zd*, long long, int, double*,

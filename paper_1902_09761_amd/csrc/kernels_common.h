@@ -79,10 +79,88 @@ __device__ __forceinline__ cx<T> lane_shift(cx<T> v) {
 // ------------------------------------------------------------------------------------------
 // reductions
 // ------------------------------------------------------------------------------------------
+// Value of lane i ^ O of the wave, O in {1, 2, 4, 8} (DPP within rows of 16 lanes).
+template <int O>
+__device__ __forceinline__ int lane_xor(int v) {
+    static_assert(O == 1 || O == 2 || O == 4 || O == 8, "one row");
+    if constexpr (O == 8) return __builtin_amdgcn_update_dpp(v, v, 0x128, 0xf, 0xf, false);        // row_ror:8
+    else if constexpr (O == 4)
+        return __builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(v, v, 0x104, 0xf, 0x5, false), v, 0x114, 0xf,
+                                           0xa, false);                                            // row_shl:4, row_shr:4
+    else return __builtin_amdgcn_update_dpp(v, v, O == 2 ? 0x4e : 0xb1, 0xf, 0xf, false);          // quad_perm
+}
+template <int O>
+__device__ __forceinline__ double lane_xor(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = lane_xor<O>((int)(b & 0xffffffffLL)), hi = lane_xor<O>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// One step of a butterfly sum over lanes i and i ^ O for two values at once: lanes with bit O clear get
+// a_i + a_{i^O}, the others b_i + b_{i^O}.
+template <int O>
+__device__ __forceinline__ double pair_step(double a, double b) {
+    if constexpr (O >= 16) {
+        const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+        auto swap = [](unsigned u, unsigned v) {
+            if constexpr (O == 32) return __builtin_amdgcn_permlane32_swap(u, v, false, false);
+            else return __builtin_amdgcn_permlane16_swap(u, v, false, false);
+        };
+        const auto lo = swap((unsigned)(x & 0xffffffffLL), (unsigned)(y & 0xffffffffLL));
+        const auto hi = swap((unsigned)(x >> 32), (unsigned)(y >> 32));
+        return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) +
+               __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+    } else {
+        const bool up = threadIdx.x & O;
+        return (up ? b : a) + lane_xor<O>(up ? a : b);
+    }
+}
+// Sum over the wave in every lane, by lanes i and i ^ o for o = 32, 16, .., 1 (lane swaps and DPP: no LDS
+// traffic).
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = pair_step<32>(v, v);
+    v = pair_step<16>(v, v);
+    v += lane_xor<8>(v);
+    v += lane_xor<4>(v);
+    v += lane_xor<2>(v);
+    v += lane_xor<1>(v);
     return v;
+}
+
+// wave_sum of NV values (the same sums, bit for bit): every step halves the values a lane carries, so all
+// together cost about NV + 6 additions instead of 6 NV.  out(i, total of value i) is called by one lane per
+// value.  v is overwritten.
+template <int O, int N, int NV>
+__device__ __forceinline__ void wave_sums_step(double (&v)[NV]) {
+#pragma unroll
+    for (int i = 0; i < (N + 1) / 2; ++i) v[i] = pair_step<O>(v[2 * i], v[2 * i + 1 < N ? 2 * i + 1 : 2 * i]);
+}
+template <int NV, typename F>
+__device__ __forceinline__ void wave_sums(double (&v)[NV], F&& out) {
+    constexpr int N1 = (NV + 1) / 2, N2 = (N1 + 1) / 2, N3 = (N2 + 1) / 2, N4 = (N3 + 1) / 2, N5 = (N4 + 1) / 2;
+    wave_sums_step<32, NV>(v);
+    wave_sums_step<16, N1>(v);
+    wave_sums_step<8, N2>(v);
+    wave_sums_step<4, N3>(v);
+    wave_sums_step<2, N4>(v);
+    wave_sums_step<1, N5>(v);
+    const int idx = (int)(__brev(threadIdx.x & 63) >> 26);   // value carried by this lane (plus 64 per entry)
+#pragma unroll
+    for (int i = 0; i < (NV + 63) / 64; ++i)
+        if (idx + 64 * i < NV) out(idx + 64 * i, v[i]);
+}
+
+// Sum NV per-thread values over the workgroup of 4 waves; out(i, total of value i) is called by thread i.
+// lds >= 4*NV.
+template <int NV, typename F>
+__device__ __forceinline__ void block_totals(double (&v)[NV], double* lds, F&& out) {
+    const int wv = threadIdx.x >> 6;
+    wave_sums<NV>(v, [&](int i, double t) { lds[wv * NV + i] = t; });
+    __syncthreads();
+    if (threadIdx.x < NV) {
+        const int i = threadIdx.x;
+        out(i, ((lds[i] + lds[NV + i]) + lds[2 * NV + i]) + lds[3 * NV + i]);
+    }
+    __syncthreads();
 }
 
 // Sum NV per-thread values over the workgroup; thread 0 receives the totals.  lds >= 4*NV.
