@@ -131,6 +131,8 @@ struct apfc_ctx {
     Tile* d_mtiles = nullptr;
     int cheb_shape = 0;
     size_t max_ctiles = 0;
+    std::vector<CTile> rtiles;         // regions of the fused 2D Jacobi-PCG preconditioner (empty: not used)
+    int pcg_rows = 0;                  // their rows per wave (kPcgRows)
     long long NT = 0, NI = 0;
     int maxn[3] = {1, 1, 1};           // largest mesh sizes over the systems
     int TY = 16;
@@ -471,7 +473,45 @@ void build_ctiles(apfc_ctx& c) {
     }
 }
 
+// Regions of the fused 2D Jacobi-PCG preconditioner, used for up to kPcgMax iterations per inner solve (the
+// halo grows by one layer per iteration, and the Gram matrices with the square) in FP64: its inner solves
+// agree with step-by-step CG to ~1e-15, but in FP32 storage with long restarts the rounding of z decides how
+// far below rtol a solve ends, and CG's own rounding is kept there.  Meshes of at most 64 x 64 nodes go to
+// launch_precond_pcg_small.
+// Rows per wave: 4 while all regions fit on the chip at once, one per CU, since a region of 8 rows per wave
+// takes twice as long; else 8, whose halo is a smaller share.  The region table lies in the work vector pc[5]
+// and the Gram partials in apart, which the one-launch-per-half-step path uses otherwise.
+CTile* rtile_table(const apfc_ctx& c) { return (CTile*)c.pc[5]; }
+void build_rtiles(apfc_ctx& c) {
+    c.rtiles.clear();
+    const apfc_params& p = c.solver;
+    const bool sep = p.mass_kind == APFC_MASS_SEPARABLE;
+    if (c.dim != 2 || p.inner_kind != APFC_INNER_PCG || p.diff_iters > kPcgMax || (!sep && p.mass_iters > kPcgMax) ||
+        c.mixed || (c.maxn[0] <= kTX && c.maxn[1] <= kTX))
+        return;
+    const int H = pcg_halo(p.mass_iters, p.diff_iters, sep), IX = kTX - 2 * H;
+    auto count = [&](int rows) {
+        const int IY = rows * (kPcgThreads / 64) - 2 * H;
+        long long n = 0;
+        for (const Sys& y : c.sys) n += (long long)((y.nx + IX - 1) / IX) * ((y.ny + IY - 1) / IY);
+        return n;
+    };
+    c.pcg_rows = count(kPcgRows[0]) <= 256 ? kPcgRows[0] : kPcgRows[1];
+    if (2 * kPcgGram * count(c.pcg_rows) > (2LL * kMaxRestart + 2) * c.max_tiles) return;
+    const int IY = c.pcg_rows * (kPcgThreads / 64) - 2 * H;
+    for (int s = 0; s < c.S; ++s) {
+        const Sys& y = c.sys[s];
+        std::vector<CTile> nat;
+        const int first = (int)c.rtiles.size();
+        for (int y0 = 0; y0 < y.ny; y0 += IY)
+            for (int x0 = 0; x0 < y.nx; x0 += IX) nat.push_back(CTile{s, x0, y0, first});
+        append_xcd_order(nat, c.rtiles);
+    }
+}
+
 int upload_tables(apfc_ctx& c) {
+    if (!c.rtiles.empty())
+        HIPCHK(hipMemcpy(rtile_table(c), c.rtiles.data(), sizeof(CTile) * c.rtiles.size(), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(c.d_sys, c.sys.data(), sizeof(Sys) * c.S, hipMemcpyHostToDevice));
     for (int l = 0; l < c.mg_n; ++l) {
         HIPCHK(hipMemcpy(c.d_mg_sys[l], c.mg_sys[l].data(), sizeof(Sys) * c.S, hipMemcpyHostToDevice));
@@ -931,6 +971,7 @@ int apfc_create_batch(int count, const apfc_mesh* meshes, const apfc_lattice* la
     c->TY = 16;
     build_tiles(*c, c->TY, c->tiles);
     set_dt_scalars(*c, 1.0);
+    build_rtiles(*c);
     if (params[0].inner_kind == APFC_INNER_CHEB && dim == 2) {
         for (int sh = 0; sh < kChebShapes; ++sh) {
             c->cheb_shape = sh;
@@ -1110,7 +1151,13 @@ void precond(apfc_ctx* c, const Dev& d, const cx<T>* v, cx<T>* z, const int* mas
     else if (c->solver.inner_kind == APFC_INNER_CHEB)
         launch_precond_cheb_unfused<T>(d, v, z, pc[0], pc[1], pc[2], pc[3], pc[4], c->solver.mass_iters,
                                        c->solver.diff_iters, sep, mask, st);
-    else
+    else if (c->dim == 2 && c->maxn[0] <= kTX && c->maxn[1] <= kTX)
+        launch_precond_pcg_small<T>(d, v, z, pc[0], pc[1], c->solver.mass_iters, c->solver.diff_iters, sep, mask, st);
+    else if (std::is_same_v<T, double> && !c->rtiles.empty()) {
+        if constexpr (std::is_same_v<T, double>)
+            launch_precond_pcg2d(d, c->pcg_rows, rtile_table(*c), (int)c->rtiles.size(), v, z, pc[0], pc[1], pc[2],
+                                 pc[3], c->apart, c->solver.mass_iters, c->solver.diff_iters, sep, mask, st);
+    } else
         launch_precond<T>(d, v, z, pc[0], pc[1], pc[2], pc[3], pc[4], pc[5], c->tpart, c->solver.mass_iters,
                           c->solver.diff_iters, sep, mask, st);
 }
@@ -1923,6 +1970,8 @@ int attach_scratch(apfc_ctx* c, hipStream_t st) {
     HIPCHK(hipMemcpyAsync(c->d_sys, c->sys.data(), sizeof(Sys) * c->S, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(c->d_tiles, c->tiles.data(), sizeof(Tile) * c->tiles.size(), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(c->d_chunks, c->chunks.data(), sizeof(Chunk) * c->chunks.size(), hipMemcpyHostToDevice, st));
+    if (!c->rtiles.empty())
+        HIPCHK(hipMemcpyAsync(rtile_table(*c), c->rtiles.data(), sizeof(CTile) * c->rtiles.size(), hipMemcpyHostToDevice, st));
     if (!c->ctiles.empty())
         HIPCHK(hipMemcpyAsync(c->d_ctiles, c->ctiles.data(), sizeof(CTile) * c->ctiles.size(), hipMemcpyHostToDevice, st));
     if (!c->mtiles.empty())
