@@ -282,6 +282,11 @@ void launch_zeta(const Dev& d, const zd* eta, zd* zeta, hipStream_t st);
 template <typename T>
 void launch_mg_vcycle(const Dev& fine, const MgLevels& mg, const cx<T>* b, cx<T>* x, cx<T>* r, cx<T>* d0, cx<T>* d1,
                       const int* mask, hipStream_t st);
+// The fused 2D cycle (kernels_mg.hip)
+int mg_tail_level(const Dev& fine, const MgLevels& mg);
+template <typename T>
+void launch_mg_fused2d(const Dev& fine, const MgLevels& mg, int tail, int rhs, const cx<T>* v, const cx<T>* src, cx<T>* b,
+                       cx<T>* x, cx<T>* xs, const cx<T>* x1, const cx<T>* x2, cx<T>* z, const int* mask, hipStream_t st);
 // The block preconditioner with the multigrid L solves: step 1 by mass_iters Chebyshev iterations (or the
 // separable mass inverse), steps 2 and 3 by one V-cycle each, step 4.
 template <typename T>

@@ -1870,18 +1870,31 @@ void launch_precond_mg(const Dev& d, const MgLevels& mg, const cx<T>* v, cx<T>* 
             }
             cb_iterations<DIM, TYv, T, 0>(d, mass_iters, d0, d1, r, x1, mask, st);
         }
+        const int tail = mg_tail_level(d, mg);
+        if (tail > 0) {
+            // steps 2 to 4 with the right-hand sides and step 4 inside the fused cycles
+            launch_mg_fused2d<T>(d, mg, tail, 1, v + d.NT, x1, b, x2, r, nullptr, nullptr, nullptr, mask, st);
+            launch_mg_fused2d<T>(d, mg, tail, 2, nullptr, x2, b, z + d.NT, r, x1, x2, z, mask, st);
+            return;
+        }
+        auto vcycle = [&](cx<T>* x) {
+            if (tail == 0)
+                launch_mg_fused2d<T>(d, mg, 0, 0, nullptr, nullptr, b, x, r, nullptr, nullptr, nullptr, mask, st);
+            else
+                launch_mg_vcycle<T>(d, mg, b, x, r, d0, d1, mask, st);
+        };
         // step 2: b = beta2 - kappa G beta1' (the stage-1 start writes it to its residual argument), one V-cycle
         {
             ProbeScope ps(d, KID_CHEB, st, (double)d.NT * 5.0 * sizeof(cx<T>), mask);
             cb_init_launch<DIM, TYv, T, 1>(d, mask, v, x1, b, d0, d1, st);
         }
-        launch_mg_vcycle<T>(d, mg, b, x2, r, d0, d1, mask, st);
+        vcycle(x2);
         // step 3: b = M beta2', one V-cycle into the eta part of z
         {
             ProbeScope ps(d, KID_CHEB, st, (double)d.NT * 4.0 * sizeof(cx<T>), mask);
             cb_init_launch<DIM, TYv, T, 2>(d, mask, v, x2, b, d0, d1, st);
         }
-        launch_mg_vcycle<T>(d, mg, b, z + d.NT, r, d0, d1, mask, st);
+        vcycle(z + d.NT);
         // step 4
         ProbeScope ps(d, KID_PC_FINAL, st);
         hipLaunchKernelGGL((k_pc_final<DIM, TYv, T>), TILE_GRID, d.sys, d.tiles, mask, x1, x2, z, d.NT);

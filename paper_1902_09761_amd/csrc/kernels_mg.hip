@@ -6,7 +6,7 @@
 // the transpose of the Q1 interpolation, and a coarsest level solved in LDS by Chebyshev iterations over
 // its whole spectrum.  One cycle from a zero initial guess:
 //     x = S(b);  r = b - L x;  x += P V(P^T r);  r = b - L x;  x += S(r).
-#include "kernels_common.h"
+#include "kernels_region.h"
 
 namespace apfc {
 
@@ -206,6 +206,392 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_coarse(const Sys* sys, const 
 }
 
 // ------------------------------------------------------------------------------------------
+// Fused 2D V-cycle, up to kMgFusedNu smoothing iterations: a level above 64 x 64 nodes takes one launch down
+// and one up on register-resident regions of 64 x 32 nodes (row_sweep), the levels below one launch for all of
+// them (k_mg_tail).  Per node the arithmetic and its rounding are those of the kernels above.  Latency bounds
+// the cycle (a level of 128 x 112 x 3 is 45 regions): 2 levels + 1 launches of 6 to 15 us and one of 35 us
+// instead of 7 launches per level of ~4.5 us each and the coarsest level's 29 us; 512 x 448 x 3, dt = 10: a step
+// of 55 FGMRES iterations 25.9 -> 12.7 ms.
+// ------------------------------------------------------------------------------------------
+constexpr int kMgFusedNu = 4, kMgNP = 4, kMgNW = 8, kMgRegY = kMgNP * kMgNW, kMgRegThreads = 64 * kMgNW;
+
+// The region of workgroup blockIdx.x of system blockIdx.y: interior tiles of (64 - 2 halo) x (kMgRegY - 2 halo)
+// nodes, row by row; false past the system's last one.
+struct MgRegion {
+    RegionRows rows0;
+    int x0, y0, ix, r0, IX, IY, nx, ny;
+    __device__ __forceinline__ bool init(const Sys& s, int halo) {
+        nx = s.nx;
+        ny = s.ny;
+        IX = kTX - 2 * halo;
+        IY = kMgRegY - 2 * halo;
+        const int nrx = (nx + IX - 1) / IX, nry = (ny + IY - 1) / IY, b = (int)blockIdx.x;
+        if (b >= nrx * nry) return false;
+        x0 = (b % nrx) * IX;
+        y0 = (b / nrx) * IY;
+        const int lane = (int)threadIdx.x & 63;
+        r0 = ((int)threadIdx.x >> 6) * kMgNP - halo;
+        ix = lane - halo;
+        rows0 = RegionRows{s.off, (long long)wrapi(x0 + ix, nx), wrapi(y0 + r0, ny), nx, ny};
+        return true;
+    }
+    __device__ __forceinline__ bool owned(int i) const {
+        const int iy = r0 + i;
+        return ix >= 0 && ix < IX && x0 + ix < nx && iy >= 0 && iy < IY && y0 + iy < ny;
+    }
+};
+
+// stencil() for a walk over rows: x passes m = mass u, k = (stiffness u) h and e = derivative u of a row, and M u,
+// K u, T u from three of them, with the contractions the compiler makes of stencil(), where a node's nine
+// values are in one block.
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <typename T>
+struct RowStencil {
+    struct Row {
+        cx<T> m, k, e;
+    };
+    T m0, m1, ih, cM, cK;
+    __device__ explicit RowStencil(const Sys& s) {
+        const T h = T(s.h);
+        m0 = h * T(1.0 / 6.0);
+        m1 = h * T(4.0 / 6.0);
+        ih = T(1) / h;
+        cM = T(s.isq_dt);
+        cK = T(s.sq_kap);
+    }
+    __device__ __forceinline__ Row row(cx<T> l, cx<T> c, cx<T> r) const {
+        return {m0 * (l + r) + m1 * c, (c + c) - (l + r), T(0.5) * (r - l)};
+    }
+    __device__ __forceinline__ cx<T> M(const Row& A, const Row& B, const Row& C) const {
+        return m0 * (A.m + C.m) + m1 * B.m;
+    }
+    __device__ __forceinline__ cx<T> K(const Row& A, const Row& B, const Row& C) const {
+        const cx<T> kc = ih * C.k;
+        const cx<T> ks{mad(ih, A.k.x, kc.x), mad(ih, A.k.y, kc.y)};
+        return (m0 * ks + m1 * (ih * B.k)) + ih * ((B.m + B.m) - (A.m + C.m));
+    }
+    __device__ __forceinline__ cx<T> Tj(const Row& A, const Row& B, const Row& C, T k0, T k1) const {
+        const cx<T> x = k0 * (m0 * (A.e + C.e) + m1 * B.e), y = T(0.5) * (C.m - A.m);
+        return cx<T>{T(2) * mad(k1, y.x, x.x), T(2) * mad(k1, y.y, x.y)};
+    }
+    __device__ __forceinline__ cx<T> L(const Row& A, const Row& B, const Row& C) const {
+        return cM * M(A, B, C) + cK * K(A, B, C);
+    }
+};
+template <typename T>
+struct Raw {
+    cx<T> l, c, r;
+};
+// sum of the 3 x 3 fine nodes with weights (1/2, 1, 1/2) x (1/2, 1, 1/2), in the order of k_mg_restrict
+template <typename T>
+__device__ __forceinline__ cx<T> mg_restrict(const Raw<T>& A, const Raw<T>& B, const Raw<T>& C) {
+    const T q = T(0.25), h = T(0.5);
+    cx<T> a = q * A.l;
+    a = a + h * A.c;
+    a = a + q * A.r;
+    a = a + h * B.l;
+    a = a + B.c;
+    a = a + h * B.r;
+    a = a + q * C.l;
+    a = a + h * C.c;
+    return a + q * C.r;
+}
+// (P x_c) at fine node (gx, gy), ld(i, j) = node (i, j) of the coarse level of nx x ny nodes, in the order of
+// k_mg_prolong
+template <typename T, typename F>
+__device__ __forceinline__ cx<T> mg_interp(int gx, int gy, int nx, int ny, F&& ld) {
+    const int i0 = gx >> 1, j0 = gy >> 1, i1 = i0 + 1 == nx ? 0 : i0 + 1, j1 = j0 + 1 == ny ? 0 : j0 + 1;
+    const bool ox = gx & 1, oy = gy & 1;
+    const T w = (ox ? T(0.5) : T(1)) * (oy ? T(0.5) : T(1));
+    cx<T> a = w * ld(i0, j0);
+    if (ox) a = a + w * ld(i1, j0);
+    if (oy) a = a + w * ld(i0, j1);
+    if (ox && oy) a = a + w * ld(i1, j1);
+    return a;
+}
+
+// Down: x = S(b) (to xs, read by the way up), r = b - L x, b_c = P^T r (to bc, the coarse level's half vector).
+// RHS 0: b = src; 1: b = v - kappa G src (step 2); 2: b = M src (step 3); formed b is stored to bout.
+template <typename T, int RHS>
+__global__ __launch_bounds__(kMgRegThreads) void k_mg_down2d(const Sys* sys, const Sys* csys, const int* mask,
+                                                            const cx<T>* v, const cx<T>* src, cx<T>* bout, cx<T>* xs,
+                                                            cx<T>* bc, int nu, int halo) {
+    __shared__ cx<T> edges[2][kMgNW][2][kTX];
+    const int si = blockIdx.y, wv = (int)threadIdx.x >> 6;
+    if (mask && !mask[si]) return;
+    const Sys& s = sys[si];
+    MgRegion reg;
+    if (!reg.init(s, halo)) return;
+    using Row = typename RowStencil<T>::Row;
+    const RowStencil<T> st(s);
+    auto make = [&](cx<T> l, cx<T> c, cx<T> r) { return st.row(l, c, r); };
+    int e = 0;
+    cx<T> B[kMgNP], R[kMgNP], D[kMgNP], X[kMgNP];
+    {
+        RegionRows g = reg.rows0;
+#pragma unroll
+        for (int i = 0; i < kMgNP; ++i, g.next()) D[i] = src[g.at()];
+    }
+    if constexpr (RHS == 0) {
+#pragma unroll
+        for (int i = 0; i < kMgNP; ++i) B[i] = D[i];
+    } else {
+        if constexpr (RHS == 1) {
+            RegionRows g = reg.rows0;
+#pragma unroll
+            for (int i = 0; i < kMgNP; ++i, g.next()) B[i] = v[g.at()];
+        }
+        const T k0 = T(s.kv[0]), k1 = T(s.kv[1]), kap = T(s.kappa);
+        row_sweep<T, kMgNP, kMgNW>(D, edges[e], wv, make, [&](int i, const Row& a, const Row& b, const Row& c, cx<T>) {
+            if constexpr (RHS == 1)
+                B[i] = B[i] - kap * gop(st.K(a, b, c), st.Tj(a, b, c, k0, k1));
+            else
+                B[i] = st.M(a, b, c);
+        });
+        e ^= 1;
+        RegionRows g = reg.rows0;
+#pragma unroll
+        for (int i = 0; i < kMgNP; ++i, g.next())
+            if (reg.owned(i)) bout[g.at()] = B[i];
+    }
+    const double(*cb)[2] = s.cb[1];
+    const T c0 = T(cb[0][0]);
+#pragma unroll
+    for (int i = 0; i < kMgNP; ++i) {
+        R[i] = B[i];
+        D[i] = c0 * B[i];
+        X[i] = D[i];
+    }
+    for (int j = 1; j < nu; ++j) {
+        const T c1 = T(cb[j][0]), c2 = T(cb[j][1]);
+        row_sweep<T, kMgNP, kMgNW>(D, edges[e], wv, make,
+                                   [&](int i, const Row& a, const Row& b, const Row& c, cx<T> dB) {
+                                       R[i] = R[i] - st.L(a, b, c);
+                                       D[i] = c1 * dB + c2 * R[i];
+                                       X[i] = X[i] + D[i];
+                                   });
+        e ^= 1;
+    }
+    {
+        RegionRows g = reg.rows0;
+#pragma unroll
+        for (int i = 0; i < kMgNP; ++i, g.next())
+            if (reg.owned(i)) xs[g.at()] = X[i];
+    }
+    row_sweep<T, kMgNP, kMgNW>(X, edges[e], wv, make, [&](int i, const Row& a, const Row& b, const Row& c, cx<T>) {
+        R[i] = B[i] - st.L(a, b, c);
+    });
+    e ^= 1;
+    const Sys& cs = csys[si];
+    row_sweep<T, kMgNP, kMgNW>(
+        R, edges[e], wv, [](cx<T> l, cx<T> c, cx<T> r) { return Raw<T>{l, c, r}; },
+        [&](int i, const Raw<T>& a, const Raw<T>& b, const Raw<T>& c, cx<T>) {
+            const int gx = reg.x0 + reg.ix, gy = reg.y0 + reg.r0 + i;
+            if (reg.owned(i) && !(gx & 1) && !(gy & 1))
+                bc[cs.off + (long long)(gy >> 1) * cs.nx + (gx >> 1)] = mg_restrict<T>(a, b, c);
+        });
+}
+
+// Up: x = xs + P x_c, r = b - L x, x += S(r).  FINAL: x is chi2 of step 3 and step 4 follows,
+// z = x1 - (x2 - chi2 / sqrt(dt)) / sqrt(kappa).
+template <typename T, bool FINAL>
+__global__ __launch_bounds__(kMgRegThreads) void k_mg_up2d(const Sys* sys, const Sys* csys, const int* mask, const cx<T>* b,
+                                                          const cx<T>* xs, const cx<T>* xc, cx<T>* x, const cx<T>* x1,
+                                                          const cx<T>* x2, cx<T>* z, int nu, int halo) {
+    __shared__ cx<T> edges[2][kMgNW][2][kTX];
+    const int si = blockIdx.y, wv = (int)threadIdx.x >> 6;
+    if (mask && !mask[si]) return;
+    const Sys& s = sys[si];
+    MgRegion reg;
+    if (!reg.init(s, halo)) return;
+    using Row = typename RowStencil<T>::Row;
+    const RowStencil<T> st(s);
+    auto make = [&](cx<T> l, cx<T> c, cx<T> r) { return st.row(l, c, r); };
+    int e = 0;
+    cx<T> R[kMgNP], D[kMgNP], X[kMgNP];
+    {
+        const Sys& c = csys[si];
+        const cx<T>* xcs = xc + c.off;
+        const int cnx = c.nx, cny = c.ny;
+        RegionRows g = reg.rows0;
+#pragma unroll
+        for (int i = 0; i < kMgNP; ++i, g.next()) {
+            R[i] = b[g.at()];
+            X[i] = xs[g.at()] +
+                   mg_interp<T>((int)g.gx, g.gy, cnx, cny, [&](int p, int q) { return xcs[(long long)q * cnx + p]; });
+        }
+    }
+    row_sweep<T, kMgNP, kMgNW>(X, edges[e], wv, make, [&](int i, const Row& p, const Row& q, const Row& w, cx<T>) {
+        R[i] = R[i] - st.L(p, q, w);
+    });
+    e ^= 1;
+    const double(*cb)[2] = s.cb[1];
+    const T c0 = T(cb[0][0]);
+#pragma unroll
+    for (int i = 0; i < kMgNP; ++i) {
+        D[i] = c0 * R[i];
+        X[i] = X[i] + D[i];
+    }
+    for (int j = 1; j < nu; ++j) {
+        const T c1 = T(cb[j][0]), c2 = T(cb[j][1]);
+        row_sweep<T, kMgNP, kMgNW>(D, edges[e], wv, make,
+                                   [&](int i, const Row& p, const Row& q, const Row& w, cx<T> dB) {
+                                       R[i] = R[i] - st.L(p, q, w);
+                                       D[i] = c1 * dB + c2 * R[i];
+                                       X[i] = X[i] + D[i];
+                                   });
+        e ^= 1;
+    }
+    RegionRows g = reg.rows0;
+#pragma unroll
+    for (int i = 0; i < kMgNP; ++i, g.next())
+        if (reg.owned(i)) {
+            const long long gi = g.at();
+            x[gi] = X[i];
+            if constexpr (FINAL) z[gi] = x1[gi] - T(s.isq_kap) * (x2[gi] - T(s.isq_dt) * X[i]);
+        }
+}
+
+// The levels of at most 64 x 64 nodes, one workgroup per system: down to the coarsest level (its Chebyshev
+// solve included) and up again, each vector in the registers of the threads (four consecutive rows of one
+// column each), stencils through LDS with one barrier.  x and b of the levels above the coarsest wait in their
+// global buffers, read back by the thread that wrote them.
+constexpr int kMgTail = 4, kMgTailThreads = 1024, kMgTailRows = 4;
+template <typename T>
+struct MgTailLevels {
+    int n;                          // levels, the last one the coarsest
+    const Sys* sys[kMgTail];
+    cx<T>* x[kMgTail];
+    cx<T>* b[kMgTail];              // b[0]: the right-hand side
+};
+
+template <typename T>
+__global__ __launch_bounds__(kMgTailThreads) void k_mg_tail(const MgTailLevels<T> lev, const int* mask, int nu,
+                                                           int coarse_its) {
+    __shared__ cx<T> buf[2][kTX * kTX];
+    const int si = blockIdx.x;
+    if (mask && !mask[si]) return;
+    const int x = (int)threadIdx.x & 63, y0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) * kMgTailRows;
+    using Row = typename RowStencil<T>::Row;
+    int set = 0;
+    // u into LDS (all rows of the level), visible after the barrier; two buffers in turn
+    auto stage = [&](const cx<T> (&u)[kMgTailRows], int nx, int ny) -> const cx<T>* {
+        cx<T>* p = buf[set];
+        set ^= 1;
+#pragma unroll
+        for (int i = 0; i < kMgTailRows; ++i)
+            if (x < nx && y0 + i < ny) p[(y0 + i) * kTX + x] = u[i];
+        __syncthreads();
+        return p;
+    };
+    // R = B - L u
+    auto residual = [&](const Sys& s, const RowStencil<T>& st, const cx<T> (&B)[kMgTailRows], const cx<T> (&u)[kMgTailRows],
+                        cx<T> (&R)[kMgTailRows]) {
+        const int nx = s.nx, ny = s.ny;
+        const cx<T>* p = stage(u, nx, ny);
+        if (y0 >= ny || x >= nx) return;
+        const int xl = x == 0 ? nx - 1 : x - 1, xr = x == nx - 1 ? 0 : x + 1;
+        Row A{}, C{};
+#pragma unroll
+        for (int a = 0; a < kMgTailRows + 2; ++a) {
+            int y = y0 - 1 + a;
+            y = y < 0 ? ny - 1 : y >= ny ? y - ny : y;
+            const cx<T>* row = p + y * kTX;
+            const Row N = st.row(row[xl], row[x], row[xr]);
+            if (a >= 2) R[a - 2] = B[a - 2] - st.L(A, C, N);
+            A = C;
+            C = N;
+        }
+    };
+    cx<T> B[kMgTailRows], R[kMgTailRows], D[kMgTailRows], X[kMgTailRows];
+    auto inside = [&](const Sys& s, int i) { return x < s.nx && y0 + i < s.ny; };
+    auto node = [&](const Sys& s, int i) { return s.off + (long long)(y0 + i) * s.nx + x; };
+#pragma unroll
+    for (int i = 0; i < kMgTailRows; ++i) {
+        B[i] = cx<T>{T(0), T(0)};
+        if (inside(lev.sys[0][si], i)) B[i] = lev.b[0][node(lev.sys[0][si], i)];
+    }
+    // Chebyshev iterations 1 .. its - 1 on R, D, X
+    auto smooth = [&](const Sys& s, const RowStencil<T>& st, int its) {
+        for (int j = 1; j < its; ++j) {
+            residual(s, st, R, D, R);
+            const T c1 = T(s.cb[1][j][0]), c2 = T(s.cb[1][j][1]);
+#pragma unroll
+            for (int i = 0; i < kMgTailRows; ++i) {
+                D[i] = c1 * D[i] + c2 * R[i];
+                X[i] = X[i] + D[i];
+            }
+        }
+    };
+    // from zero: R = B, D = X = c0 B
+    auto start = [&](const Sys& s) {
+        const T c0 = T(s.cb[1][0][0]);
+#pragma unroll
+        for (int i = 0; i < kMgTailRows; ++i) {
+            R[i] = B[i];
+            D[i] = c0 * B[i];
+            X[i] = D[i];
+        }
+    };
+    for (int l = 0; l + 1 < lev.n; ++l) {
+        const Sys& s = lev.sys[l][si];
+        const Sys& c = lev.sys[l + 1][si];
+        const RowStencil<T> st(s);
+        start(s);
+        smooth(s, st, nu);
+#pragma unroll
+        for (int i = 0; i < kMgTailRows; ++i)
+            if (inside(s, i)) {
+                lev.x[l][node(s, i)] = X[i];
+                if (l > 0) lev.b[l][node(s, i)] = B[i];
+            }
+        residual(s, st, B, X, R);
+        // restriction: coarse node (x, y0 + i) from the fine nodes around (2 x, 2 (y0 + i))
+        const int fnx = s.nx, fny = s.ny;
+        const cx<T>* p = stage(R, fnx, fny);
+#pragma unroll
+        for (int i = 0; i < kMgTailRows; ++i) {
+            B[i] = cx<T>{T(0), T(0)};
+            if (!inside(c, i)) continue;
+            const int fx = 2 * x, fy = 2 * (y0 + i), xl = fx == 0 ? fnx - 1 : fx - 1, yl = fy == 0 ? fny - 1 : fy - 1;
+            auto raw = [&](int y) { return Raw<T>{p[y * kTX + xl], p[y * kTX + fx], p[y * kTX + fx + 1]}; };
+            B[i] = mg_restrict<T>(raw(yl), raw(fy), raw(fy + 1));
+        }
+    }
+    {
+        const Sys& s = lev.sys[lev.n - 1][si];
+        start(s);
+        smooth(s, RowStencil<T>(s), coarse_its);
+    }
+    for (int l = lev.n - 2; l >= 0; --l) {
+        const Sys& s = lev.sys[l][si];
+        const int cnx = lev.sys[l + 1][si].nx, cny = lev.sys[l + 1][si].ny;
+        const RowStencil<T> st(s);
+        const cx<T>* p = stage(X, cnx, cny);
+#pragma unroll
+        for (int i = 0; i < kMgTailRows; ++i) {
+            X[i] = B[i] = R[i] = cx<T>{T(0), T(0)};
+            if (!inside(s, i)) continue;
+            X[i] = lev.x[l][node(s, i)] + mg_interp<T>(x, y0 + i, cnx, cny, [&](int a, int b) { return p[b * kTX + a]; });
+            B[i] = lev.b[l][node(s, i)];
+        }
+        residual(s, st, B, X, R);
+        const T c0 = T(s.cb[1][0][0]);
+#pragma unroll
+        for (int i = 0; i < kMgTailRows; ++i) {
+            D[i] = c0 * R[i];
+            X[i] = X[i] + D[i];
+        }
+        smooth(s, st, nu);
+    }
+    const Sys& s = lev.sys[0][si];
+#pragma unroll
+    for (int i = 0; i < kMgTailRows; ++i)
+        if (inside(s, i)) lev.x[0][node(s, i)] = X[i];
+}
+
+// ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
 // smoothing on one level: from zero (ADD = false, b given) or as a correction from the residual r
@@ -230,6 +616,73 @@ static void mg_smooth(const Dev& d, int nu, const cx<T>* b, cx<T>* r, cx<T>* d0,
                                D[j & 1], r, x);
     }
 }
+
+// The fused 2D cycle: its first level of at most 64 x 64 nodes in every system, or -1 (3D, many smoothing
+// iterations, a coarsest level above 64 x 64).
+int mg_tail_level(const Dev& fine, const MgLevels& mg) {
+    if (fine.dim != 2 || mg.nu > kMgFusedNu) return -1;
+    for (int l = 0; l <= mg.n; ++l)
+        if ((fine.maxn[0] >> l) <= kTX && (fine.maxn[1] >> l) <= kTX) return mg.n - l < kMgTail ? l : -1;
+    return -1;
+}
+
+// x = V(b); rhs 1 and 2: the fine level's b is formed from src (k_mg_down2d), with a tail below the fine level.
+// xs: work vector of the fine level.  x1 and x2 set: step 4 as well.
+template <typename T>
+void launch_mg_fused2d(const Dev& fine, const MgLevels& mg, int tail, int rhs, const cx<T>* v, const cx<T>* src, cx<T>* b,
+                       cx<T>* x, cx<T>* xs, const cx<T>* x1, const cx<T>* x2, cx<T>* z, const int* mask, hipStream_t st) {
+    auto dev = [&](int l) -> const Dev& { return l == 0 ? fine : mg.lev[l - 1]; };
+    auto B = [&](int l) { return l == 0 ? b : (cx<T>*)mg.b[l - 1]; };
+    auto X = [&](int l) { return l == 0 ? x : (cx<T>*)mg.x[l - 1]; };
+    auto XS = [&](int l) { return l == 0 ? xs : (cx<T>*)mg.r[l - 1]; };
+    auto grid = [&](int l, int halo) {
+        const int IX = kTX - 2 * halo, IY = kMgRegY - 2 * halo;
+        const int nx = fine.maxn[0] >> l, ny = fine.maxn[1] >> l;
+        return dim3(((nx + IX - 1) / IX) * ((ny + IY - 1) / IY), fine.S);
+    };
+    const double cb = sizeof(cx<T>);
+    for (int l = 0; l < tail; ++l) {
+        const Dev& d = dev(l);
+        const int form = l == 0 ? rhs : 0, halo = mg.nu + 1 + (form ? 1 : 0);
+        ProbeScope ps(d, KID_MG, st, (double)d.NT * cb * (form == 0 ? 2.25 : form == 1 ? 4.25 : 3.25), mask);
+        auto go = [&](auto rc) {
+            hipLaunchKernelGGL((k_mg_down2d<T, decltype(rc)::value>), grid(l, halo), dim3(kMgRegThreads), 0, st, d.sys,
+                               dev(l + 1).sys, mask, v, form ? src : (const cx<T>*)B(l), B(l), XS(l), B(l + 1), mg.nu,
+                               halo);
+        };
+        if (form == 1) go(std::integral_constant<int, 1>{});
+        else if (form == 2) go(std::integral_constant<int, 2>{});
+        else go(std::integral_constant<int, 0>{});
+    }
+    {
+        const Dev& d = dev(tail);
+        MgTailLevels<T> t{};
+        t.n = mg.n + 1 - tail;
+        for (int l = 0; l < t.n; ++l) {
+            t.sys[l] = dev(tail + l).sys;
+            t.x[l] = X(tail + l);
+            t.b[l] = B(tail + l);
+        }
+        ProbeScope ps(d, KID_MG, st, (double)d.NT * cb * 4.0, mask);
+        hipLaunchKernelGGL(k_mg_tail<T>, dim3(d.S), dim3(kMgTailThreads), 0, st, t, mask, mg.nu, mg.coarse_its);
+    }
+    for (int l = tail - 1; l >= 0; --l) {
+        const Dev& d = dev(l);
+        const bool fin = l == 0 && x1;
+        ProbeScope ps(d, KID_MG, st, (double)d.NT * cb * (fin ? 6.25 : 3.25), mask);
+        auto go = [&](auto fc) {
+            hipLaunchKernelGGL((k_mg_up2d<T, decltype(fc)::value>), grid(l, mg.nu), dim3(kMgRegThreads), 0, st, d.sys,
+                               dev(l + 1).sys, mask, (const cx<T>*)B(l), (const cx<T>*)XS(l), (const cx<T>*)X(l + 1), X(l),
+                               x1, x2, z, mg.nu, mg.nu);
+        };
+        if (fin) go(std::true_type{});
+        else go(std::false_type{});
+    }
+}
+template void launch_mg_fused2d<double>(const Dev&, const MgLevels&, int, int, const zd*, const zd*, zd*, zd*, zd*,
+                                        const zd*, const zd*, zd*, const int*, hipStream_t);
+template void launch_mg_fused2d<float>(const Dev&, const MgLevels&, int, int, const zf*, const zf*, zf*, zf*, zf*,
+                                       const zf*, const zf*, zf*, const int*, hipStream_t);
 
 template <typename T>
 void launch_mg_vcycle(const Dev& fine, const MgLevels& mg, const cx<T>* b, cx<T>* x, cx<T>* r, cx<T>* d0, cx<T>* d1,

@@ -58,6 +58,32 @@ __device__ __forceinline__ void reg_sweep(cx<T> (&u)[NP], cx<T> (*edge)[2][kTX],
     }
 }
 
+// The same walk with the x pass left to the caller: make(l, c, r) forms a row's pass from a node and its x
+// neighbours, f(i, A, B, C, uB) gets the passes of rows y - 1, y, y + 1 and the node's value.
+template <typename T, int NP, int NW, typename MAKE, typename F>
+__device__ __forceinline__ void row_sweep(cx<T> (&u)[NP], cx<T> (*edge)[2][kTX], int w, MAKE&& make, F&& f) {
+    const int lane = (int)threadIdx.x & (kTX - 1);
+    edge[w][0][lane] = u[0];
+    edge[w][1][lane] = u[NP - 1];
+    __syncthreads();
+    const cx<T> zero{T(0), T(0)};
+    const cx<T> above = w > 0 ? edge[w - 1][1][lane] : zero;
+    const cx<T> below = w + 1 < NW ? edge[w + 1][0][lane] : zero;
+    auto pass = [&](cx<T> c) { return make(lane_shift<kDppWaveShr1>(c), c, lane_shift<kDppWaveShl1>(c)); };
+    auto A = pass(above);
+    auto B = pass(u[0]);
+    cx<T> uB = u[0];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const cx<T> uC = i + 1 < NP ? u[i + 1] : below;
+        auto C = pass(uC);
+        f(i, A, B, C, uB);
+        A = B;
+        B = C;
+        uB = uC;
+    }
+}
+
 struct SplitCoef {
     double a, b, c, d;
 };

@@ -88,3 +88,18 @@ def test_mg_steps_match_oracle(precision):
     err = rel_l2(from_dev(et), ref)
     print("mg steps", precision, "iterations", its, "rel-L2", err)
     assert err < 1e-9
+
+
+@pytest.mark.parametrize("precision,tol", [(apfc.APFC_FP64, 1e-12), (apfc.APFC_MIXED, 2e-5)])
+@pytest.mark.parametrize("n,nu", [((208, 144), 2), ((224, 96), 4), ((112, 48), 1), ((64, 128), 5)])
+def test_mg_fused_levels_match_oracle(n, nu, precision, tol):
+    """Two fused levels above the ones solved by one workgroup (208 x 144, 104 x 72, then 52 x 36 and 26 x 18);
+    region interiors filled exactly and with remainders; the longest fused smoothing; the unfused path beyond
+    it (nu = 5)."""
+    mesh = inputs.Mesh(2, (n[0], n[1], 1), (n[0] * H_TRI, n[1] * H_TRI, 1.0))
+    assert _pinv([mesh], apfc.APFC_TRI2D, tri_k(), precision, nu, 7.0) <= tol
+
+
+def test_mg_fused_levels_batched():
+    meshes = [inputs.Mesh(2, (n, m, 1), (n * H_TRI, m * H_TRI, 1.0)) for n, m in ((192, 80), (96, 160), (64, 64))]
+    assert _pinv(meshes, apfc.APFC_TRI2D, tri_k(), apfc.APFC_FP64, 2, 3.0, max_levels=3) <= 1e-12
