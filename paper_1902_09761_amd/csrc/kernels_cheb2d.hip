@@ -366,6 +366,162 @@ __global__ __launch_bounds__(NTH, sizeof(T) == 4 ? 4 : 2) void k_cheb2d(
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// The three stages in one launch, for meshes whose regions all fit on the chip at once (kChebAllRegions): a
+// workgroup carries its 64 x 32 region through all of them in registers, with a halo of all their layers (9 for
+// three taps and three L iterations, interior 46 x 14).  x1 and x2 never leave the workgroup and two of three
+// launches go, against 3.2 times the stencil work of the interior; with more regions than CUs that work, not
+// latency, is what counts.  130 x 118 x 3 in FP32: 24.1 us in three launches, 15.8 us in one.
+// ------------------------------------------------------------------------------------------
+constexpr int kChebAllNP = 8, kChebAllNW = 4, kChebAllRegions = 256, kChebAllHalo = 10;
+
+// SEP: x1 by the separable mass inverse of MR taps; else sM Chebyshev iterations (MR = 0)
+template <typename T, int MR>
+__global__ __launch_bounds__(64 * kChebAllNW) void k_cheb2d_all(const Sys* sys, const int* mask, const cx<T>* v, cx<T>* z,
+                                                               int sM, int sL, int halo, long long NT, VIn<T> vin) {
+    constexpr int NP = kChebAllNP, NW = kChebAllNW, RL = MR > 0 ? NP * NW + 2 * MR : 1;
+    __shared__ cx<T> edges[2][NW][2][kTX];
+    __shared__ cx<T> rows[RL * kTX];   // region rows with MR rows of padding above and below (mass filter)
+    const int si = blockIdx.y, wv = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    if (mask && !mask[si]) return;
+    const Sys& s = sys[si];
+    Region<NP, NW> reg;
+    if (!reg.init(s, halo)) return;
+    int e = 0;
+    cx<T> R[NP], B2[NP], X1[NP], X2[NP], D[NP];
+    auto load_in = [&](long long hoff, cx<T> (&out)[NP]) {
+        RegionRows g = reg.rows0;
+        if (!vin.src) {
+#pragma unroll
+            for (int i = 0; i < NP; ++i, g.next()) out[i] = v[hoff + g.at()];
+            return;
+        }
+        const double* hc = vin.hcoef + (long long)si * vin.hld;
+        const double sc = vin.scale[si];
+        zd u[NP];
+        long long gi[NP];
+#pragma unroll
+        for (int i = 0; i < NP; ++i, g.next()) {
+            gi[i] = hoff + g.at();
+            u[i] = ld<double>(vin.src, gi[i]);
+        }
+        for (int l = 0; l < vin.nv; ++l) {
+            const zd c{hc[2 * l], hc[2 * l + 1]};
+            const cx<T>* Vl = vin.V + l * vin.vs;
+#pragma unroll
+            for (int i = 0; i < NP; ++i) u[i] = u[i] - cmul(c, ld<double>(Vl, gi[i]));
+        }
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            out[i] = cx<T>{T(sc * u[i].x), T(sc * u[i].y)};
+            if (reg.owned(i)) vin.vout[gi[i]] = out[i];
+        }
+    };
+    // its Chebyshev iterations on OP = M or L from zero for the right-hand side R, into X
+    auto cheb = [&](auto mc, int its, cx<T> (&X)[NP]) {
+        constexpr bool isM = decltype(mc)::value;
+        const double(*cb)[2] = s.cb[isM ? 0 : 1];
+        const SplitCoef oc = split_coef(s.h, isM ? 1.0 : s.isq_dt, isM ? 0.0 : s.sq_kap);
+        const T oa = T(oc.a), ob = T(oc.b), occ = T(oc.c), od = T(oc.d), d0 = T(cb[0][0]);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            D[i] = d0 * R[i];
+            X[i] = D[i];
+        }
+        for (int k = 1; k < its; ++k) {
+            const T c1 = T(cb[k][0]), c2 = T(cb[k][1]);
+            reg_sweep<T, NP, NW, false>(D, edges[e], wv, [&](int i, cx<T> pA, cx<T> pB, cx<T> pC, cx<T> uA, cx<T> uB,
+                                                             cx<T> uC, cx<T>, cx<T>, cx<T>) {
+                cx<T> q = R[i] - oa * (pA + pC) - ob * pB;
+                if constexpr (!isM) q = q - occ * (uA + uC) - od * uB;
+                R[i] = q;
+                const cx<T> dv = c1 * uB + c2 * q;
+                X[i] = X[i] + dv;
+                D[i] = dv;
+            });
+            e ^= 1;
+        }
+    };
+    load_in(0, R);
+    load_in(NT, B2);
+    // step 1
+    if constexpr (MR > 0) {
+        static_assert(2 * MR <= NP, "a thread's block holds the rows its neighbours need");
+        auto row = [&](int i) -> cx<T>& { return rows[(wv * NP + MR + i) * kTX + lane]; };
+        // the padding only feeds the outermost halo rows
+        for (int q = threadIdx.x; q < MR * kTX; q += 64 * NW) rows[q] = rows[(RL - MR) * kTX + q] = cx<T>{T(0), T(0)};
+        T w[MR + 1];
+#pragma unroll
+        for (int k = 0; k <= MR; ++k) w[k] = T(s.wsep[k]);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            cx<T> lo = R[i], hi = R[i], acc = w[0] * R[i];
+#pragma unroll
+            for (int k = 1; k <= MR; ++k) {
+                lo = lane_shift<kDppWaveShr1>(lo);
+                hi = lane_shift<kDppWaveShl1>(hi);
+                acc = acc + w[k] * (lo + hi);
+            }
+            D[i] = acc;
+            if (i < MR || i >= NP - MR) row(i) = acc;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            cx<T> acc = w[0] * D[i];
+#pragma unroll
+            for (int k = 1; k <= MR; ++k) {
+                const cx<T> a = i - k >= 0 ? D[i - k] : row(i - k);
+                const cx<T> b = i + k < NP ? D[i + k] : row(i + k);
+                acc = acc + w[k] * (a + b);
+            }
+            X1[i] = acc;
+        }
+    } else {
+        cheb(std::true_type{}, sM, X1);
+    }
+    // step 2
+    {
+        const T k3 = T(s.kappa / 3.0), k4 = T(4.0 * s.kappa), kap = T(s.kappa);
+        const T g0 = T(s.kappa * s.h / 6.0 * s.kv[0]), g1 = T(s.kappa * s.h / 6.0 * s.kv[1]);
+        reg_sweep<T, NP, NW, true>(X1, edges[e], wv, [&](int i, cx<T> pA, cx<T> pB, cx<T> pC, cx<T> uA, cx<T> uB, cx<T> uC,
+                                                         cx<T> eA, cx<T> eB, cx<T> eC) {
+            const cx<T> kk = kap * (uA + uC) + k4 * uB - k3 * ((pA + pC) + pB);
+            const cx<T> tt = g0 * (T(4) * eB + (eA + eC)) + g1 * (pC - pA);
+            R[i] = B2[i] + cx<T>{kk.x + tt.y, kk.y - tt.x};
+        });
+        e ^= 1;
+    }
+    cheb(std::false_type{}, sL, X2);
+    // steps 3 and 4
+    {
+        const SplitCoef m = split_coef(s.h, 1.0, 0.0);
+        const T ma = T(m.a), mb = T(m.b);
+        reg_sweep<T, NP, NW, false>(X2, edges[e], wv, [&](int i, cx<T> pA, cx<T> pB, cx<T> pC, cx<T>, cx<T>, cx<T>, cx<T>,
+                                                          cx<T>, cx<T>) { R[i] = ma * (pA + pC) + mb * pB; });
+        e ^= 1;
+    }
+    cx<T>(&chi2)[NP] = B2;
+    cheb(std::false_type{}, sL, chi2);
+    RegionRows g = reg.rows0;
+#pragma unroll
+    for (int i = 0; i < NP; ++i, g.next())
+        if (reg.owned(i)) {
+            const long long gi = g.at();
+            z[gi] = X1[i] - T(s.isq_kap) * (X2[i] - T(s.isq_dt) * chi2[i]);
+            z[NT + gi] = chi2[i];
+        }
+}
+
+// Halo and grid of k_cheb2d_all; grid.x = 0 where it does not apply.
+static dim3 cheb_all_grid(const Dev& d, int mass_iters, int diff_iters, int mass_sep, int& halo) {
+    halo = (mass_sep > 0 ? mass_sep : mass_iters - 1) + 2 * diff_iters;
+    if (halo > kChebAllHalo) return dim3(0);
+    const int IX = kTX - 2 * halo, IY = kChebAllNP * kChebAllNW - 2 * halo;
+    const long long n = (long long)((d.maxn[0] + IX - 1) / IX) * ((d.maxn[1] + IY - 1) / IY);
+    return n * d.S <= kChebAllRegions ? dim3((unsigned)n, d.S) : dim3(0);
+}
+
 template <typename T, int RX, int RY, int NTH>
 static void cheb_stages(const Dev& d, const CTile* ctiles, int nctiles, int halo, const cx<T>* v, cx<T>* z,
                         cx<T>* x1, cx<T>* x2, int mass_iters, int diff_iters, int mass_sep, const VIn<T>& vin,
@@ -403,6 +559,26 @@ template <typename T>
 void launch_precond_cheb(const Dev& d, int shape, const CTile* ctiles, int nctiles, int halo, const cx<T>* v,
                          cx<T>* z, cx<T>* x1, cx<T>* x2, int mass_iters, int diff_iters, int mass_sep,
                          const VIn<T>& vin, const int* mask, hipStream_t st) {
+    int halo_all = 0;
+    // with many basis vectors the halo's share of their loads outweighs the saved launches
+    const dim3 all = vin.nv <= 8 ? cheb_all_grid(d, mass_iters, diff_iters, mass_sep, halo_all) : dim3(0);
+    if (all.x > 0) {
+        const double c = sizeof(cx<T>), in = c * (vin.src ? 2 + vin.nv : 1);
+        ProbeScope ps(d, KID_CHEB, st, (double)d.NT * 2.0 * (in + c), mask, true);
+        auto go = [&](auto mr) {
+            ps.launch(k_cheb2d_all<T, decltype(mr)::value>, all, dim3(64 * kChebAllNW), d.sys, mask, v, z, mass_iters,
+                      diff_iters, halo_all, d.NT, vin);
+        };
+        static_assert(kMassRMax == 4, "one case per tap count");
+        switch (mass_sep) {
+            case 0: go(std::integral_constant<int, 0>{}); break;
+            case 1: go(std::integral_constant<int, 1>{}); break;
+            case 2: go(std::integral_constant<int, 2>{}); break;
+            case 3: go(std::integral_constant<int, 3>{}); break;
+            default: go(std::integral_constant<int, 4>{}); break;
+        }
+        return;
+    }
 #define APFC_CHEB_SHAPE(I)                                                                                       \
     case I:                                                                                                      \
         cheb_stages<T, kChebShape[I][0], kChebShape[I][1], kChebShape[I][2]>(                                    \

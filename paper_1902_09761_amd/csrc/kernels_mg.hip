@@ -215,31 +215,7 @@ __global__ __launch_bounds__(kMgThreads) void k_mg_coarse(const Sys* sys, const 
 // ------------------------------------------------------------------------------------------
 constexpr int kMgFusedNu = 4, kMgNP = 4, kMgNW = 8, kMgRegY = kMgNP * kMgNW, kMgRegThreads = 64 * kMgNW;
 
-// The region of workgroup blockIdx.x of system blockIdx.y: interior tiles of (64 - 2 halo) x (kMgRegY - 2 halo)
-// nodes, row by row; false past the system's last one.
-struct MgRegion {
-    RegionRows rows0;
-    int x0, y0, ix, r0, IX, IY, nx, ny;
-    __device__ __forceinline__ bool init(const Sys& s, int halo) {
-        nx = s.nx;
-        ny = s.ny;
-        IX = kTX - 2 * halo;
-        IY = kMgRegY - 2 * halo;
-        const int nrx = (nx + IX - 1) / IX, nry = (ny + IY - 1) / IY, b = (int)blockIdx.x;
-        if (b >= nrx * nry) return false;
-        x0 = (b % nrx) * IX;
-        y0 = (b / nrx) * IY;
-        const int lane = (int)threadIdx.x & 63;
-        r0 = ((int)threadIdx.x >> 6) * kMgNP - halo;
-        ix = lane - halo;
-        rows0 = RegionRows{s.off, (long long)wrapi(x0 + ix, nx), wrapi(y0 + r0, ny), nx, ny};
-        return true;
-    }
-    __device__ __forceinline__ bool owned(int i) const {
-        const int iy = r0 + i;
-        return ix >= 0 && ix < IX && x0 + ix < nx && iy >= 0 && iy < IY && y0 + iy < ny;
-    }
-};
+using MgRegion = Region<kMgNP, kMgNW>;
 
 // stencil() for a walk over rows: x passes m = mass u, k = (stiffness u) h and e = derivative u of a row, and M u,
 // K u, T u from three of them, with the contractions the compiler makes of stencil(), where a node's nine

@@ -101,4 +101,31 @@ struct RegionRows {
     __device__ __forceinline__ void next() { gy = gy + 1 == ny ? 0 : gy + 1; }
 };
 
+// The region of workgroup blockIdx.x of system blockIdx.y, 64 x (NP NW) nodes with `halo` layers around an interior
+// tile, tiles row by row; init: false past the system's last one.
+template <int NP, int NW>
+struct Region {
+    RegionRows rows0;
+    int x0, y0, ix, r0, IX, IY, nx, ny;
+    __device__ __forceinline__ bool init(const Sys& s, int halo) {
+        nx = s.nx;
+        ny = s.ny;
+        IX = kTX - 2 * halo;
+        IY = NP * NW - 2 * halo;
+        const int nrx = (nx + IX - 1) / IX, nry = (ny + IY - 1) / IY, b = (int)blockIdx.x;
+        if (b >= nrx * nry) return false;
+        x0 = (b % nrx) * IX;
+        y0 = (b / nrx) * IY;
+        const int lane = (int)threadIdx.x & 63;
+        r0 = ((int)threadIdx.x >> 6) * NP - halo;
+        ix = lane - halo;
+        rows0 = RegionRows{s.off, (long long)wrapi(x0 + ix, nx), wrapi(y0 + r0, ny), nx, ny};
+        return true;
+    }
+    __device__ __forceinline__ bool owned(int i) const {
+        const int iy = r0 + i;
+        return ix >= 0 && ix < IX && x0 + ix < nx && iy >= 0 && iy < IY && y0 + iy < ny;
+    }
+};
+
 }  // namespace apfc
