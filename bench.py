@@ -41,13 +41,13 @@ sys.path.insert(0, ROOT)
 METRIC = "amplitude DOF-steps/s at 1e-8 rel. residual + % HBM peak; plain vs mixed/batch"
 HBM_PEAK_GBS = 8000.0
 CSRC = os.path.join(ROOT, "paper_1902_09761_amd", "csrc")
-KERNEL_SOURCES = ["apfc_internal.h", "kernels_common.h", "kernels.hip", "kernels_apply.hip", "kernels_cheb2d.hip",
-                  "kernels_mg.hip", "kernels_mass.hip"]
+KERNEL_SOURCES = ["apfc_internal.h", "kernels_common.h", "kernels_region.h", "kernels.hip", "kernels_apply.hip",
+                  "kernels_cheb2d.hip", "kernels_mg.hip", "kernels_mass.hip"]
 PROFILES = os.path.join(ROOT, "profiles")
 # kernel families with a byte model, as the library's probe names them, and the kernels they cover
 FAMILIES = {"cheb": "k_cheb2d (3D: k_cb_*)", "apply": "k_apply_dot2d/3d", "proj_final": "k_proj_final",
             "residual": "k_residual2d/3d", "extrapolate": "k_extrapolate", "rhs": "k_rhs_nonlinear",
-            "pcg_spmv": "k_cg_spmv", "pcg_update": "k_cg_update", "mass": "k_mass_sep"}
+            "pcg_spmv": "k_cg_spmv (2D FP64: k_pcg2d, k_pcg_small)", "pcg_update": "k_cg_update", "mass": "k_mass_sep"}
 
 
 def parse():

@@ -478,8 +478,8 @@ void build_ctiles(apfc_ctx& c) {
 // agree with step-by-step CG to ~1e-15, but in FP32 storage with long restarts the rounding of z decides how
 // far below rtol a solve ends, and CG's own rounding is kept there.  Meshes of at most 64 x 64 nodes go to
 // launch_precond_pcg_small.
-// Rows per wave: 4 while all regions fit on the chip at once, one per CU, since a region of 8 rows per wave
-// takes twice as long; else 8, whose halo is a smaller share.  The region table lies in the work vector pc[5]
+// Rows per wave: 4 up to 1.5 regions per CU, since a region of 8 rows per wave takes twice as long (250 x 234 x 3,
+// 360 regions: 3.28 ms per step against 3.50); else 8, whose halo is a smaller share (256^2 x 3, 396: equal).  The region table lies in the work vector pc[5]
 // and the Gram partials in apart, which the one-launch-per-half-step path uses otherwise.
 CTile* rtile_table(const apfc_ctx& c) { return (CTile*)c.pc[5]; }
 void build_rtiles(apfc_ctx& c) {
@@ -496,7 +496,7 @@ void build_rtiles(apfc_ctx& c) {
         for (const Sys& y : c.sys) n += (long long)((y.nx + IX - 1) / IX) * ((y.ny + IY - 1) / IY);
         return n;
     };
-    c.pcg_rows = count(kPcgRows[0]) <= 256 ? kPcgRows[0] : kPcgRows[1];
+    c.pcg_rows = count(kPcgRows[0]) <= 384 ? kPcgRows[0] : kPcgRows[1];
     if (2 * kPcgGram * count(c.pcg_rows) > (2LL * kMaxRestart + 2) * c.max_tiles) return;
     const int IY = c.pcg_rows * (kPcgThreads / 64) - 2 * H;
     for (int s = 0; s < c.S; ++s) {

@@ -57,6 +57,10 @@ __device__ __forceinline__ void stv(cx<S>* p, long long i, cx<R> v) {
     p[i] = cx<S>{S(v.x), S(v.y)};
 }
 
+// a b + c rounded once, where the place of the rounding matters
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // Whole-wave lane shifts by one lane (DPP wave_shr:1 / wave_shl:1): after lane_shift<kDppWaveShr1>, lane i
 // holds lane i - 1's value (lane 0 gets 0); after kDppWaveShl1, lane i + 1's (lane 63 gets 0).
 constexpr int kDppWaveShl1 = 0x130, kDppWaveShr1 = 0x138;

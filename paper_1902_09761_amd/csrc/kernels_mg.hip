@@ -220,8 +220,6 @@ using MgRegion = Region<kMgNP, kMgNW>;
 // stencil() for a walk over rows: x passes m = mass u, k = (stiffness u) h and e = derivative u of a row, and M u,
 // K u, T u from three of them, with the contractions the compiler makes of stencil(), where a node's nine
 // values are in one block.
-__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 template <typename T>
 struct RowStencil {
     struct Row {

@@ -285,8 +285,6 @@ __device__ __forceinline__ double div_by(double v, double D, double y) {
     return __builtin_fma(__builtin_fma(-q, D, v), y, q);
 }
 
-__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 // a value equal in every lane, moved to scalar registers (the kernel below is short of vector registers)
 __device__ __forceinline__ float uniform(float v) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
