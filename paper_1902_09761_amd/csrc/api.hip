@@ -426,6 +426,14 @@ int cheb_halo(const apfc_params& p) {
     return std::max(p.mass_kind == APFC_MASS_SEPARABLE ? p.mass_iters : p.mass_iters - 1, p.diff_iters);
 }
 
+// CUs of the current device (without one: of a whole MI355X)
+int device_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 256;
+    return std::max(1, cus);
+}
+
 // Bricks of the separable mass inverse and of the 3D Chebyshev L solves: 64 x kMassBY nodes per plane;
 // in 3D, bz = kBrickZShallow or kBrickZDeep planes, whichever gives the smaller (workgroup rounds) x (bz + 2
 // planes marched per brick), a round being as many bricks as the chip holds at once: deeper bricks re-read
@@ -441,11 +449,9 @@ void build_mtiles(apfc_ctx& c) {
         }
         return n;
     };
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus = 256;
+    const int cus = device_cus();
     auto cost = [&](int bz) {
-        const long long slots = (long long)std::max(1, cus) * std::max(1, brick_occupancy(bz, c.mixed));
+        const long long slots = (long long)cus * std::max(1, brick_occupancy(bz, c.mixed));
         return (count(bz) + slots - 1) / slots * (bz + 2);
     };
     c.mbz = c.dim == 3 && cost(kBrickZDeep) < cost(kBrickZShallow) ? kBrickZDeep : kBrickZShallow;
@@ -473,32 +479,40 @@ void build_ctiles(apfc_ctx& c) {
     }
 }
 
-// Regions of the fused 2D Jacobi-PCG preconditioner, used for up to kPcgMax iterations per inner solve (the
-// halo grows by one layer per iteration, and the Gram matrices with the square) in FP64: its inner solves
-// agree with step-by-step CG to ~1e-15, but in FP32 storage with long restarts the rounding of z decides how
-// far below rtol a solve ends, and CG's own rounding is kept there.  Meshes of at most 64 x 64 nodes go to
-// launch_precond_pcg_small.
-// Rows per wave: 4 up to 1.5 regions per CU, since a region of 8 rows per wave takes twice as long (250 x 234 x 3,
-// 360 regions: 3.28 ms per step against 3.50); else 8, whose halo is a smaller share (256^2 x 3, 396: equal).  The region table lies in the work vector pc[5]
-// and the Gram partials in apart, which the one-launch-per-half-step path uses otherwise.
+// Regions of the 2D Jacobi-PCG preconditioner with one launch per step: FP64 and up to kPcgMax iterations per inner solve,
+// where it was compared with the two launches per step that sum <p, OP p> in a pass of its own (kernels_pcg2d.hip).  In
+// FP32 storage with long restarts the rounding of z decides how far below rtol a solve ends, and CG's own rounding is
+// kept there.  Meshes of at most 64 x 64 nodes go to launch_precond_pcg_small.
+// Rows per wave (kPcgRows): the fewest that leave at most one region per CU, where latency counts and a taller region
+// takes longer (P^{-1} of 180 x 170 x 3 by 2, 4, 8 rows: 104, 120, 150 us; 320^2 x 3: 150, 143, 178; 512^2 x 3: 295, 260,
+// 237).  Where none does, 4 rows (1024^2 x 3: 1237, 842, 840 us; 24 meshes of 250 x 234 x 3: 1228, 1166, 1267), or 8 on
+// systems of more than 2^20 nodes, where the halo's share of the traffic counts (1200^2 x 3 by 4, 8 rows: 1308, 1239 us;
+// 2048^2 x 3: 5137, 4090).
+// The region table lies in the work vector pc[5] and the partials in apart, which the two-launch path uses otherwise.
 CTile* rtile_table(const apfc_ctx& c) { return (CTile*)c.pc[5]; }
 void build_rtiles(apfc_ctx& c) {
     c.rtiles.clear();
     const apfc_params& p = c.solver;
-    const bool sep = p.mass_kind == APFC_MASS_SEPARABLE;
-    if (c.dim != 2 || p.inner_kind != APFC_INNER_PCG || p.diff_iters > kPcgMax || (!sep && p.mass_iters > kPcgMax) ||
-        c.mixed || (c.maxn[0] <= kTX && c.maxn[1] <= kTX))
+    if (c.dim != 2 || p.inner_kind != APFC_INNER_PCG || p.diff_iters > kPcgMax ||
+        (p.mass_kind != APFC_MASS_SEPARABLE && p.mass_iters > kPcgMax) || c.mixed || (c.maxn[0] <= kTX && c.maxn[1] <= kTX))
         return;
-    const int H = pcg_halo(p.mass_iters, p.diff_iters, sep), IX = kTX - 2 * H;
+    const int IX = kTX - 2 * kPcgHalo;
+    auto interior = [](int rows) { return rows * (kPcgThreads / 64) - 2 * kPcgHalo; };
     auto count = [&](int rows) {
-        const int IY = rows * (kPcgThreads / 64) - 2 * H;
+        const int IY = interior(rows);
         long long n = 0;
         for (const Sys& y : c.sys) n += (long long)((y.nx + IX - 1) / IX) * ((y.ny + IY - 1) / IY);
         return n;
     };
-    c.pcg_rows = count(kPcgRows[0]) <= 384 ? kPcgRows[0] : kPcgRows[1];
-    if (2 * kPcgGram * count(c.pcg_rows) > (2LL * kMaxRestart + 2) * c.max_tiles) return;
-    const int IY = c.pcg_rows * (kPcgThreads / 64) - 2 * H;
+    const int cus = device_cus();
+    c.pcg_rows = c.NT > (1LL << 20) * c.S ? kPcgRows[2] : kPcgRows[1];
+    for (int rows : kPcgRows)
+        if (count(rows) <= cus) {
+            c.pcg_rows = rows;
+            break;
+        }
+    if (2 * kPcgSums * count(c.pcg_rows) > (2LL * kMaxRestart + 2) * c.max_tiles) return;
+    const int IY = interior(c.pcg_rows);
     for (int s = 0; s < c.S; ++s) {
         const Sys& y = c.sys[s];
         std::vector<CTile> nat;
@@ -1155,8 +1169,8 @@ void precond(apfc_ctx* c, const Dev& d, const cx<T>* v, cx<T>* z, const int* mas
         launch_precond_pcg_small<T>(d, v, z, pc[0], pc[1], c->solver.mass_iters, c->solver.diff_iters, sep, mask, st);
     else if (std::is_same_v<T, double> && !c->rtiles.empty()) {
         if constexpr (std::is_same_v<T, double>)
-            launch_precond_pcg2d(d, c->pcg_rows, rtile_table(*c), (int)c->rtiles.size(), v, z, pc[0], pc[1], pc[2],
-                                 pc[3], c->apart, c->solver.mass_iters, c->solver.diff_iters, sep, mask, st);
+            launch_precond_pcg2d(d, c->pcg_rows, rtile_table(*c), (int)c->rtiles.size(), v, z, (zd**)c->pc,
+                                 c->apart, c->solver.mass_iters, c->solver.diff_iters, sep, mask, st);
     } else
         launch_precond<T>(d, v, z, pc[0], pc[1], pc[2], pc[3], pc[4], pc[5], c->tpart, c->solver.mass_iters,
                           c->solver.diff_iters, sep, mask, st);

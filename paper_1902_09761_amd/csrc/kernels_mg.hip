@@ -217,42 +217,6 @@ constexpr int kMgFusedNu = 4, kMgNP = 4, kMgNW = 8, kMgRegY = kMgNP * kMgNW, kMg
 
 using MgRegion = Region<kMgNP, kMgNW>;
 
-// stencil() for a walk over rows: x passes m = mass u, k = (stiffness u) h and e = derivative u of a row, and M u,
-// K u, T u from three of them, with the contractions the compiler makes of stencil(), where a node's nine
-// values are in one block.
-template <typename T>
-struct RowStencil {
-    struct Row {
-        cx<T> m, k, e;
-    };
-    T m0, m1, ih, cM, cK;
-    __device__ explicit RowStencil(const Sys& s) {
-        const T h = T(s.h);
-        m0 = h * T(1.0 / 6.0);
-        m1 = h * T(4.0 / 6.0);
-        ih = T(1) / h;
-        cM = T(s.isq_dt);
-        cK = T(s.sq_kap);
-    }
-    __device__ __forceinline__ Row row(cx<T> l, cx<T> c, cx<T> r) const {
-        return {m0 * (l + r) + m1 * c, (c + c) - (l + r), T(0.5) * (r - l)};
-    }
-    __device__ __forceinline__ cx<T> M(const Row& A, const Row& B, const Row& C) const {
-        return m0 * (A.m + C.m) + m1 * B.m;
-    }
-    __device__ __forceinline__ cx<T> K(const Row& A, const Row& B, const Row& C) const {
-        const cx<T> kc = ih * C.k;
-        const cx<T> ks{mad(ih, A.k.x, kc.x), mad(ih, A.k.y, kc.y)};
-        return (m0 * ks + m1 * (ih * B.k)) + ih * ((B.m + B.m) - (A.m + C.m));
-    }
-    __device__ __forceinline__ cx<T> Tj(const Row& A, const Row& B, const Row& C, T k0, T k1) const {
-        const cx<T> x = k0 * (m0 * (A.e + C.e) + m1 * B.e), y = T(0.5) * (C.m - A.m);
-        return cx<T>{T(2) * mad(k1, y.x, x.x), T(2) * mad(k1, y.y, x.y)};
-    }
-    __device__ __forceinline__ cx<T> L(const Row& A, const Row& B, const Row& C) const {
-        return cM * M(A, B, C) + cK * K(A, B, C);
-    }
-};
 template <typename T>
 struct Raw {
     cx<T> l, c, r;

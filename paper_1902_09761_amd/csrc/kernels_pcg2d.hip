@@ -5,120 +5,69 @@
 namespace apfc {
 
 // ------------------------------------------------------------------------------------------
-// K steps of Jacobi-PCG from a zero start on OP (constant diagonal D) give the vector of the Krylov space
-// span{b, OP b, .., OP^{K-1} b} with the smallest OP-norm error, so the two inner products per step need not
-// be taken one after the other: with t_i = T_i(A) b, A = (D^{-1} OP - theta) / delta the operator mapped to
-// [-1, 1] (exact symbol bounds theta -+ delta) and T_i the Chebyshev polynomials, the result is
-//   x = sum_{i < K} c_i t_i,   H c = g,   H_ij = <t_i, OP t_j>,   g_i = <t_i, b>,
-// and A t_j = (t_{j-1} + t_{j+1}) / 2 (t_1 for j = 0) gives H from the Gram matrix of t_0 .. t_K.  A solve is
-// then two halves without a global reduction inside: the Gram matrix of its right-hand side (partials per
-// region), and, in the next launch, the K x K system and the sum over the t_i, formed again from b.  The
-// Chebyshev basis keeps H well conditioned; a direction whose pivot is lost to rounding (b in a smaller
-// invariant space, where CG has converged already) is left out together with the later ones.
+// Meshes above 64 x 64 nodes, FP64: one launch per CG step.  With the residual r and the direction p = r / D + beta p_old
+// a step needs beta = <r, r> / <r_old, r_old> and alpha = (<r, r> / D) / <p, OP p>.  The directions are OP-orthogonal, so
+//   <p, OP p> = <r, OP r> / D^2 - beta^2 <p_old, OP p_old>,   1 / alpha = <r, OP r> / (D <r, r>) - beta / alpha_old,
+// and both scalars follow from two sums over r alone: a launch takes a whole step (p, x, r) with the sums of the launch
+// before it, applies OP to the new r and leaves its two sums, one partial of each per region.  Against 80-bit
+// arithmetic a P^{-1} is as accurate as with <p, OP p> summed in a pass of its own (2e-16 rms on amplitude fields).
+// Taking a solve's coefficients from the Gram matrix of its Krylov vectors would save launches, but loses up to eight
+// digits on smooth right-hand sides, where those vectors are nearly parallel; the sums over the new direction and
+// its image, expanded into ones known a launch earlier, lose a bit or two where the residual drops fast.
 //
-// A workgroup holds a region of 64 x 8 NP nodes = interior + `halo` layers in registers (reg_sweep; one wave
-// per NP rows), each stencil application exact one layer further in.  Launches per application of P^{-1}:
-//   STAGE 0: Gram matrix of beta1                              (mass solve)
-//   STAGE 1: x1 from it; r2 = beta2 - kappa G x1, its Gram matrix (SEP: x1 given)
-//   STAGE 2: x2 from it; r3 = M x2, its Gram matrix
-//   STAGE 3: chi2 from it; step 4
-// Latency bounds them at the sizes they are used for (108 regions on 256^2 x 3: one per CU): four launches of
-// 11 + 35 + 35 + 15 us stand for the 30 launches (~150 us) that one launch per CG half-step takes.
+// A workgroup holds a region of 64 x 8 NP nodes, interior plus kPcgHalo layers, in registers (row_sweep; one wave per
+// NP rows): OP p on the interior and one layer around it (instead of storing it), OP r on the interior.  Launches per
+// application of P^{-1}, K steps per solve:
+//   PCG_MASS  r = beta1                                              (SEP: x1 given)
+//   PCG_STEP  K - 1 times
+//   PCG_G     last step's x1; r = beta2 - kappa G x1
+//   PCG_STEP  K - 1 times
+//   PCG_M     last step's x2; r = M x2
+//   PCG_STEP  K - 1 times
+//   PCG_END   last step's chi2; step 4
+// K = 3 and 5: 14 launches instead of the 30 of two launches per step.  Small meshes are bound by launches and latency
+// (96 x 80 x 3: 174 us -> 91 us), large ones by memory: a step moves 6 vectors instead of 10 (1024^2 x 3: 1568 us ->
+// 842 us; 2048^2 x 3: 12.0 ms -> 4.1 ms).
 // ------------------------------------------------------------------------------------------
+enum { PCG_MASS, PCG_STEP, PCG_G, PCG_M, PCG_END };
 
-// Gram pair (i, j), i <= j, of t_0 .. t_K as slot j (j + 1) / 2 + i
-__host__ __device__ constexpr int gram_slot(int i, int j) { return j * (j + 1) / 2 + i; }
-
-// The K coefficients c of one solve from the Gram matrix G (slots; pair (K, K) not needed), for the operator
-// with diagonal D and scaled spectrum theta -+ delta.  One thread.
-__device__ void krylov_coef(const double* G, int K, double D, double theta, double delta, double* c) {
-    constexpr int KM = kPcgMax;
-    const double tol = 1e-14;   // pivots below tol H_00 are rounding
-    double L[KM][KM], d[KM], y[KM];
-    auto g = [&](int i, int j) { return i <= j ? G[gram_slot(i, j)] : G[gram_slot(j, i)]; };
-    auto at = [&](int i, int j) { return j == 0 ? g(i, 1) : 0.5 * (g(i, j - 1) + g(i, j + 1)); };
-    int n = 0;
-    bool more = true;
-#pragma unroll
-    for (int j = 0; j < KM; ++j) {
-        c[j] = 0.0;
-        if (j >= K || !more) continue;
-        // row j of H (i <= j) and the pivot; L row-wise
-        double row[KM];
-#pragma unroll
-        for (int i = 0; i <= j; ++i) {
-            double h = theta * g(i, j) + 0.5 * delta * (at(i, j) + at(j, i));
-#pragma unroll
-            for (int q = 0; q < i; ++q) h -= L[i][q] * row[q];
-            row[i] = h;                                  // L_ji d_i (i < j), d_j (i = j)
-        }
-        double piv = theta * g(j, j) + delta * at(j, j);
-        double yv = g(0, j);
-#pragma unroll
-        for (int q = 0; q < j; ++q) {
-            const double l = row[q] * d[q];              // d holds the inverse pivots
-            piv -= l * row[q];
-            L[j][q] = l;
-            yv -= l * y[q];
-        }
-        if (!(piv > tol * (theta * g(0, 0) + delta * g(0, 1)))) {
-            more = false;
-            continue;
-        }
-        d[j] = 1.0 / piv;
-        y[j] = yv;
-        n = j + 1;
-    }
-#pragma unroll
-    for (int i = KM - 1; i >= 0; --i) {
-        if (i >= n) continue;
-        double v = y[i] * d[i];
-#pragma unroll
-        for (int q = i + 1; q < KM; ++q)
-            if (q < n) v -= L[q][i] * c[q];
-        c[i] = v;
-    }
-#pragma unroll
-    for (int i = 0; i < KM; ++i) c[i] = i < n ? c[i] / D : 0.0;
-}
-
-// OP mapped to [-1, 1] in split form: A u = a (pA + pC) + b pB + c (uA + uC) + d uB
-struct MappedOp {
-    double a, b, c, d;
+// One launch's vectors.  x, r, p: iterate before this launch's step, its residual, the direction before it (x and p
+// null: the solve's first step); xo, ro, po: iterate, new residual and direction (PCG_G, PCG_M: ro the next solve's
+// right-hand side).  xo must not be x where a neighbour still reads x (PCG_G, PCG_M); r, p and ro, po are different
+// vectors.
+struct PcgVecs {
+    const zd *x, *r, *p;
+    zd *xo, *ro, *po;
 };
-__device__ __forceinline__ MappedOp mapped_op(const Sys& s, bool isM) {
-    const SplitCoef o = split_coef(s.h, isM ? 1.0 : s.isq_dt, isM ? 0.0 : s.sq_kap);
-    const double th = isM ? s.thM : s.thL, de = isM ? s.deM : s.deL, D = isM ? s.diagM : s.diagL;
-    const double f = 1.0 / (D * de);
-    return {f * o.a, f * o.b, f * o.c, f * o.d - th / de};
-}
 
-template <int NP, int STAGE, bool SEP>
-__global__ __launch_bounds__(kPcgThreads, 2) void k_pcg2d(const Sys* sys, const CTile* tiles, const int* mask,
-                                                         const zd* v, zd* x1, zd* x2, zd* r2, zd* r3, zd* z, int KM1,
-                                                         int KL, int halo, long long NT, const double* gin,
-                                                         double* gout, int nreg) {
+// Partials of a region b: g[b] = <r, r>, g[nreg + b] = <r, OP r>; at a system's first region also its <r, r> and alpha
+// of the step before, g[2 nreg + b] and g[3 nreg + b].
+template <int NP, int KIND, bool isM>
+__global__ __launch_bounds__(kPcgThreads) void k_pcg2d(const Sys* sys, const CTile* tiles, const int* mask, const PcgVecs a,
+                                                      const zd* v, zd* z, long long NT, const double* gin, double* gout,
+                                                      int nreg) {
     using T = double;
-    constexpr int KM = kPcgMax, NW = kPcgThreads / 64, RX = kTX, RY = NP * NW;
-    constexpr bool SOLVE = STAGE >= 1 && !(STAGE == 1 && SEP), GRAM = STAGE <= 2;
+    using Row = RowStencil<T>::Row;
+    constexpr int NW = kPcgThreads / 64, IX = kTX - 2 * kPcgHalo, IY = NP * NW - 2 * kPcgHalo;
     __shared__ zd edges[2][NW][2][kTX];
-    __shared__ double sums[kPcgGram], coef[KM], part[GRAM ? NW : 1][kPcgGram];
+    __shared__ double sums[2], part[NW][2];
     const CTile tile = tiles[blockIdx.x];
     if (mask && !mask[tile.sys]) return;
     const Sys& s = sys[tile.sys];
     const int nx = s.nx, ny = s.ny, lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
-    const int IX = RX - 2 * halo, IY = RY - 2 * halo, r0 = wv * NP;
-    const RegionRows rows0{s.off, (long long)wrapi(tile.x0 - halo + lane, nx), wrapi(tile.y0 - halo + r0, ny), nx, ny};
-    const int ix = lane - halo;
+    const int ix = lane - kPcgHalo, r0 = wv * NP - kPcgHalo;
+    const RegionRows rows0{s.off, (long long)wrapi(tile.x0 + ix, nx), wrapi(tile.y0 + r0, ny), nx, ny};
     const bool own_x = ix >= 0 && ix < IX && tile.x0 + ix < nx;
-    auto owned = [&](int i) {
-        const int iy = r0 + i - halo;
-        return own_x && iy >= 0 && iy < IY && tile.y0 + iy < ny;
-    };
+    auto owned = [&](int i) { return own_x && r0 + i >= 0 && r0 + i < IY && tile.y0 + r0 + i < ny; };
     auto load = [&](const zd* src, zd (&u)[NP]) {
         RegionRows g = rows0;
 #pragma unroll
         for (int i = 0; i < NP; ++i, g.next()) u[i] = src[g.at()];
+    };
+    auto load_owned = [&](const zd* src, zd (&u)[NP]) {
+        RegionRows g = rows0;
+#pragma unroll
+        for (int i = 0; i < NP; ++i, g.next()) u[i] = owned(i) ? src[g.at()] : zd{0.0, 0.0};
     };
     auto store = [&](zd* dst, const zd (&u)[NP]) {
         RegionRows g = rows0;
@@ -126,144 +75,95 @@ __global__ __launch_bounds__(kPcgThreads, 2) void k_pcg2d(const Sys* sys, const 
         for (int i = 0; i < NP; ++i, g.next())
             if (owned(i)) dst[g.at()] = u[i];
     };
-    int e = 0;   // edge set of the next sweep (two sets in turn: one barrier per sweep)
-    // t_{i+1} (out) = f A t_i - (i > 0 ? t_{i-1} : 0), f = 1 for i = 0 and 2 after it
-    auto advance = [&](const MappedOp& o, bool isM, T f, zd (&t)[NP], auto&& out) {
-        const T a = f * T(o.a), b = f * T(o.b), cc = f * T(o.c), dd = f * T(o.d);
-        reg_sweep<T, NP, NW, false>(t, edges[e], wv, [&](int i, zd pA, zd pB, zd pC, zd uA, zd uB,
-                                                         zd uC, zd, zd, zd) {
-            zd q = a * (pA + pC) + b * pB + dd * uB;
-            if (!isM) q = q + cc * (uA + uC);
-            out(i, uB, q);
-        });
-        e ^= 1;
-    };
-    zd r[NP];   // the right-hand side whose Gram matrix this stage forms
-    if constexpr (SOLVE) {
-        constexpr bool isM = STAGE == 1;
-        const int K = isM ? KM1 : KL;
-        zd U[NP], P[NP], X[NP];
-        load(STAGE == 1 ? v : STAGE == 2 ? r2 : r3, U);
-        // the system's Gram matrix: its regions' partials in a fixed order (tile.z = its first region)
-        {
-            const int n = ((nx + IX - 1) / IX) * ((ny + IY - 1) / IY);
-            for (int q = wv; q < gram_slot(K, K); q += NW) {
-                double a = 0.0;
-                for (int t = lane; t < n; t += 64) a += gin[(long long)q * nreg + tile.z + t];
-                a = wave_sum(a);
-                if (lane == 0) sums[q] = a;
-            }
-            __syncthreads();
-            if (threadIdx.x == 0)
-                krylov_coef(sums, K, isM ? s.diagM : s.diagL, isM ? s.thM : s.thL, isM ? s.deM : s.deL, coef);
-            __syncthreads();
+    zd R[NP], P[NP], X[NP];
+    double alpha = 0.0, rho = 0.0;
+    if (KIND != PCG_MASS && a.r) {
+        load(a.r, R);
+        if (a.p) load(a.p, P);
+        if (a.x) {
+            if constexpr (KIND == PCG_STEP || KIND == PCG_END) load_owned(a.x, X);   // xo may be x
+            else load(a.x, X);
         }
-        const MappedOp o = mapped_op(s, isM);
-        const T c0 = T(coef[0]);
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            X[i] = c0 * U[i];
-            P[i] = zd{T(0), T(0)};
-        }
-        for (int k = 1; k < K; ++k) {
-            const T c = T(coef[k]);
-            advance(o, isM, k == 1 ? T(1) : T(2), U, [&](int i, zd tk, zd q) {
-                const zd tn = q - P[i];
-                P[i] = tk;
-                U[i] = tn;
-                X[i] = X[i] + c * tn;
-            });
-        }
-        if constexpr (STAGE == 3) {
-            const T isd = T(s.isq_dt), isk = T(s.isq_kap);
-            RegionRows g = rows0;
-#pragma unroll
-            for (int i = 0; i < NP; ++i, g.next())
-                if (owned(i)) {
-                    const long long gi = g.at();
-                    z[gi] = x1[gi] - isk * (x2[gi] - isd * X[i]);
-                    z[NT + gi] = X[i];
-                }
-            return;
-        }
-        store(STAGE == 1 ? x1 : x2, X);
-#pragma unroll
-        for (int i = 0; i < NP; ++i) U[i] = X[i];
-        if constexpr (STAGE == 1) {
-            load(v + NT, r);
-        }
-        const T k3 = T(s.kappa / 3.0), k4 = T(4.0 * s.kappa), kap = T(s.kappa);
-        const T g0 = T(s.kappa * s.h / 6.0 * s.kv[0]), g1 = T(s.kappa * s.h / 6.0 * s.kv[1]);
-        const SplitCoef m = split_coef(s.h, 1.0, 0.0);
-        const T ma = T(m.a), mb = T(m.b);
-        reg_sweep<T, NP, NW, STAGE == 1>(U, edges[e], wv, [&](int i, zd pA, zd pB, zd pC, zd uA, zd uB,
-                                                              zd uC, zd eA, zd eB, zd eC) {
-            if constexpr (STAGE == 1) {
-                const zd kk = kap * (uA + uC) + k4 * uB - k3 * ((pA + pC) + pB);
-                const zd tt = g0 * (T(4) * eB + (eA + eC)) + g1 * (pC - pA);
-                r[i] = r[i] + zd{kk.x + tt.y, kk.y - tt.x};
-            } else {
-                r[i] = ma * (pA + pC) + mb * pB;
-            }
-        });
-        e ^= 1;
-        store(STAGE == 1 ? r2 : r3, r);
-    } else if constexpr (STAGE == 0) {
-        load(v, r);
-    } else {
-        // the separable mass inverse has formed x1
-        zd U[NP];
-        load(x1, U);
-        load(v + NT, r);
-        const T k3 = T(s.kappa / 3.0), k4 = T(4.0 * s.kappa), kap = T(s.kappa);
-        const T g0 = T(s.kappa * s.h / 6.0 * s.kv[0]), g1 = T(s.kappa * s.h / 6.0 * s.kv[1]);
-        reg_sweep<T, NP, NW, true>(U, edges[e], wv, [&](int i, zd pA, zd pB, zd pC, zd uA, zd uB,
-                                                        zd uC, zd eA, zd eB, zd eC) {
-            const zd kk = kap * (uA + uC) + k4 * uB - k3 * ((pA + pC) + pB);
-            const zd tt = g0 * (T(4) * eB + (eA + eC)) + g1 * (pC - pA);
-            r[i] = r[i] + zd{kk.x + tt.y, kk.y - tt.x};
-        });
-        e ^= 1;
-        store(r2, r);
-    }
-    if constexpr (GRAM) {
-        constexpr bool isM = STAGE == 0;
-        const int K = isM ? KM1 : KL;
-        const MappedOp o = mapped_op(s, isM);
-        zd t[KM + 1][NP];
-#pragma unroll
-        for (int i = 0; i < NP; ++i) t[0][i] = r[i];
-#pragma unroll
-        for (int j = 0; j <= KM; ++j) {
-            if (j > K) continue;
-            if (j > 0)
-                advance(o, isM, j == 1 ? T(1) : T(2), t[j > 0 ? j - 1 : 0], [&](int i, zd, zd q) {
-                    t[j][i] = j > 1 ? q - t[j > 1 ? j - 2 : 0][i] : q;
-                });
-            double acc[KM + 1];
-#pragma unroll
-            for (int q = 0; q <= j; ++q) acc[q] = 0.0;
-#pragma unroll
-            for (int i = 0; i < NP; ++i)
-                if (owned(i)) {
-                    const double re = t[j][i].x, im = t[j][i].y;
-#pragma unroll
-                    for (int q = 0; q <= j; ++q) acc[q] += double(t[q][i].x) * re + double(t[q][i].y) * im;
-                }
-#pragma unroll
-            for (int q = 0; q <= j; ++q)
-                if (gram_slot(q, j) < kPcgGram) {   // pair (KM, KM) is not needed
-                    const double w = wave_sum(acc[q]);
-                    if (lane == 0) part[wv][gram_slot(q, j)] = w;
-                }
+        // the sums over the system: its regions' partials in a fixed order (tile.z = its first region)
+        const double* g = gin + tile.z;
+        const double rho_old = a.p ? g[2LL * nreg] : 0.0, alpha_old = a.p ? g[3LL * nreg] : 0.0;
+        const int n = ((nx + IX - 1) / IX) * ((ny + IY - 1) / IY);
+        if (wv < 2) {
+            double t = 0.0;
+            for (int i = lane; i < n; i += 64) t += g[(long long)wv * nreg + i];
+            t = wave_sum(t);
+            if (lane == 0) sums[wv] = t;
         }
         __syncthreads();
-        if ((int)threadIdx.x < gram_slot(K, K)) {
-            double a = 0.0;
+        // D: of the operator that the step's solve belongs to
+        const double D = isM ? s.diagM : s.diagL, iD = 1.0 / D;
+        rho = sums[0];
+        const double beta = rho_old != 0.0 ? rho / rho_old : 0.0;
+        const double ia = rho != 0.0 ? sums[1] / (D * rho) - (alpha_old != 0.0 ? beta / alpha_old : 0.0) : 0.0;
+        alpha = ia != 0.0 ? 1.0 / ia : 0.0;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) a += part[w][threadIdx.x];
-            gout[(long long)threadIdx.x * nreg + blockIdx.x] = a;
+        for (int i = 0; i < NP; ++i) {
+            P[i] = a.p ? iD * R[i] + beta * P[i] : iD * R[i];
+            X[i] = a.x ? X[i] + alpha * P[i] : alpha * P[i];
         }
+    } else if constexpr (KIND == PCG_G) {
+        load(a.x, X);   // the separable mass inverse has formed x1
+    }
+    if constexpr (KIND == PCG_END) {
+        const T isd = s.isq_dt, isk = s.isq_kap;
+        RegionRows g = rows0;
+#pragma unroll
+        for (int i = 0; i < NP; ++i, g.next())
+            if (owned(i)) {
+                const long long gi = g.at();
+                z[gi] = z[gi] - isk * (z[NT + gi] - isd * X[i]);   // x1 and x2 wait in z
+                z[NT + gi] = X[i];
+            }
+        return;
+    }
+    const RowStencil<T> op(s);
+    auto make = [&](zd l, zd c, zd r) { return op.row(l, c, r); };
+    // out(i, OP u, u) at every row, OP = M (mass) or L
+    auto apply = [&](auto mass, zd (*edge)[2][kTX], zd (&u)[NP], auto&& out) {
+        row_sweep<T, NP, NW>(u, edge, wv, make, [&](int i, const Row& A, const Row& B, const Row& C, zd uB) {
+            out(i, decltype(mass)::value ? op.M(A, B, C) : op.L(A, B, C), uB);
+        });
+    };
+    if constexpr (KIND == PCG_MASS) {
+        load(v, R);
+    } else {
+        store(a.xo, X);
+        if constexpr (KIND == PCG_STEP) {
+            store(a.po, P);
+            apply(std::bool_constant<isM>{}, edges[0], P, [&](int i, zd q, zd) { R[i] = R[i] - alpha * q; });
+        } else if constexpr (KIND == PCG_G) {
+            load(v + NT, R);
+            const T k0 = s.kv[0], k1 = s.kv[1], kap = s.kappa;
+            row_sweep<T, NP, NW>(X, edges[0], wv, make, [&](int i, const Row& A, const Row& B, const Row& C, zd) {
+                R[i] = R[i] - kap * gop(op.K(A, B, C), op.Tj(A, B, C, k0, k1));
+            });
+        } else {
+            apply(std::true_type{}, edges[0], X, [&](int i, zd q, zd) { R[i] = q; });
+        }
+        store(a.ro, R);
+    }
+    // the next step's sums
+    double acc[2] = {0.0, 0.0};
+    apply(std::bool_constant<KIND == PCG_MASS || (KIND == PCG_STEP && isM)>{}, edges[1], R, [&](int i, zd w, zd r) {
+        if (!owned(i)) return;
+        acc[0] += abs2(r);
+        acc[1] += r.x * w.x + r.y * w.y;
+    });
+    wave_sums<2>(acc, [&](int i, double t) { part[wv][i] = t; });
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += part[w][threadIdx.x];
+        gout[(long long)threadIdx.x * nreg + blockIdx.x] = t;
+    } else if (threadIdx.x == 2 && (int)blockIdx.x == tile.z) {
+        gout[2LL * nreg + blockIdx.x] = rho;
+        gout[3LL * nreg + blockIdx.x] = alpha;
     }
 }
 
@@ -501,44 +401,64 @@ template void launch_precond_pcg_small<double>(const Dev&, const zd*, zd*, zd*, 
 template void launch_precond_pcg_small<float>(const Dev&, const zf*, zf*, zf*, zf*, int, int, int, const int*,
                                               hipStream_t);
 
-// Halo of the fused regions: stage 1 forms x1 (mass_iters - 1 layers), G x1 and diff_iters layers of t_i;
-// stage 2 x2, M x2 and the t_i.
-int pcg_halo(int mass_iters, int diff_iters, bool sep) {
-    const int s1 = (sep ? 0 : mass_iters - 1) + 1 + diff_iters, s2 = 2 * diff_iters;
-    return s1 > s2 ? s1 : s2;
-}
-
 template <int NP>
-static void pcg_stages(const Dev& d, const CTile* tiles, int nreg, const zd* v, zd* z, zd* x1, zd* x2, zd* r2, zd* r3,
-                       double* gram, int mass_iters, int diff_iters, int mass_sep, const int* mask, hipStream_t st) {
-    const int halo = pcg_halo(mass_iters, diff_iters, mass_sep > 0);
-    const dim3 g(nreg), b(kPcgThreads);
-    double* G[2] = {gram, gram + (long long)kPcgGram * nreg};
-    const double vec = (double)d.NT * sizeof(zd);
-    auto go = [&](auto stage, auto sep, double vecs, const double* gin, double* gout) {
-        ProbeScope ps(d, KID_PCG_SPMV, st, vec * vecs, mask, true);
-        ps.launch(k_pcg2d<NP, decltype(stage)::value, decltype(sep)::value>, g, b, d.sys, tiles, mask, v, x1, x2,
-                  r2, r3, z, mass_iters, diff_iters, halo, d.NT, gin, gout, nreg);
-    };
+static void pcg_launches(const Dev& d, const CTile* tiles, int nreg, const zd* v, zd* z, zd* const* w, double* part,
+                         int mass_iters, int diff_iters, int mass_sep, const int* mask, hipStream_t st) {
     using std::integral_constant;
+    const double vec = (double)d.NT * sizeof(zd);
+    double* G[2] = {part, part + (long long)kPcgSums * nreg};
+    zd *x = w[0], *R[2] = {w[1], w[2]}, *P[2] = {w[3], w[4]};
+    PcgVecs a{};
+    int g = 0;
+    auto go = [&](auto kind, auto mass, double vecs) {
+        ProbeScope ps(d, KID_PCG_SPMV, st, vec * vecs, mask, true);
+        ps.launch(k_pcg2d<NP, decltype(kind)::value, decltype(mass)::value>, dim3(nreg), dim3(kPcgThreads), d.sys, tiles,
+                  mask, a, v, z, d.NT, G[g], G[g ^ 1], nreg);
+        g ^= 1;
+    };
+    // steps 1 .. n - 1 of a solve for the right-hand side r, whose sums the launch before has left
+    auto steps = [&](auto mass, int n, const zd* r) {
+        a = PcgVecs{nullptr, r, nullptr, x, nullptr, nullptr};
+        int b = r == R[0] ? 1 : 0;
+        for (int k = 1; k < n; ++k, b ^= 1) {
+            a.ro = R[b];
+            a.po = P[b];
+            go(integral_constant<int, PCG_STEP>{}, mass, a.p ? 6.0 : 4.0);
+            a = PcgVecs{x, a.ro, a.po, x, nullptr, nullptr};
+        }
+    };
+    // where the next solve's right-hand side goes
+    auto next = [&](zd* xo) {
+        a.xo = xo;
+        return a.ro = a.r == R[0] ? R[1] : R[0];
+    };
+    const zd* r;
     if (mass_sep > 0) {
-        launch_mass_sep<double>(d, mass_sep, v, x1, mask, st);
-        go(integral_constant<int, 1>{}, std::true_type{}, 3.0, nullptr, G[1]);
+        launch_mass_sep<double>(d, mass_sep, v, x, mask, st);
+        a.x = x;
+        r = next(z);
+        go(integral_constant<int, PCG_G>{}, std::true_type{}, 4.0);
     } else {
-        go(integral_constant<int, 0>{}, std::false_type{}, 1.0, nullptr, G[0]);
-        go(integral_constant<int, 1>{}, std::false_type{}, 4.0, G[0], G[1]);
+        go(integral_constant<int, PCG_MASS>{}, std::true_type{}, 1.0);
+        steps(std::true_type{}, mass_iters, v);
+        r = next(z);
+        go(integral_constant<int, PCG_G>{}, std::true_type{}, a.p ? 6.0 : 4.0);
     }
-    go(integral_constant<int, 2>{}, std::false_type{}, 3.0, G[1], G[0]);
-    go(integral_constant<int, 3>{}, std::false_type{}, 5.0, G[0], nullptr);
+    steps(std::false_type{}, diff_iters, r);
+    r = next(z + d.NT);
+    go(integral_constant<int, PCG_M>{}, std::false_type{}, a.p ? 5.0 : 3.0);
+    steps(std::false_type{}, diff_iters, r);
+    go(integral_constant<int, PCG_END>{}, std::false_type{}, a.p ? 7.0 : 5.0);
 }
 
-void launch_precond_pcg2d(const Dev& d, int rows, const CTile* tiles, int nreg, const zd* v, zd* z, zd* x1, zd* x2,
-                          zd* r2, zd* r3, double* gram, int mass_iters, int diff_iters, int mass_sep, const int* mask,
-                          hipStream_t st) {
+void launch_precond_pcg2d(const Dev& d, int rows, const CTile* tiles, int nreg, const zd* v, zd* z, zd* const* w, double* part,
+                          int mass_iters, int diff_iters, int mass_sep, const int* mask, hipStream_t st) {
     if (rows == kPcgRows[0])
-        pcg_stages<kPcgRows[0]>(d, tiles, nreg, v, z, x1, x2, r2, r3, gram, mass_iters, diff_iters, mass_sep, mask, st);
+        pcg_launches<kPcgRows[0]>(d, tiles, nreg, v, z, w, part, mass_iters, diff_iters, mass_sep, mask, st);
+    else if (rows == kPcgRows[1])
+        pcg_launches<kPcgRows[1]>(d, tiles, nreg, v, z, w, part, mass_iters, diff_iters, mass_sep, mask, st);
     else
-        pcg_stages<kPcgRows[1]>(d, tiles, nreg, v, z, x1, x2, r2, r3, gram, mass_iters, diff_iters, mass_sep, mask, st);
+        pcg_launches<kPcgRows[2]>(d, tiles, nreg, v, z, w, part, mass_iters, diff_iters, mass_sep, mask, st);
 }
 
 }  // namespace apfc

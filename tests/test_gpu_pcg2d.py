@@ -1,5 +1,5 @@
-"""The fused 2D Jacobi-PCG preconditioners (regions in registers, each inner solve from the Gram matrix of its
-Krylov space; meshes of at most 64 x 64 nodes by one workgroup per system) against the oracle's step-by-step conjugate gradients.  Needs an MI355X."""
+"""The 2D Jacobi-PCG preconditioners (one launch per step on regions in registers; meshes of at most 64 x 64 nodes by
+one workgroup per system) against the oracle's conjugate gradients.  Needs an MI355X."""
 import numpy as np
 import pytest
 
@@ -92,6 +92,41 @@ def test_small_invariant_spaces(kind):
         assert not np.any(got[0][0]) and not np.any(got[0][1])
     else:
         assert _worst([m], pairs, got, (3, 5)) <= 1e-6
+
+
+@pytest.mark.parametrize("n,its,dt", [((250, 234), (3, 5), 1.0), ((250, 234), (3, 5), 10.0), ((96, 80), (2, 4), 0.1)])
+@pytest.mark.parametrize("kind", ["grain", "mode+1e-4", "mode+1e-6"])
+def test_smooth_right_hand_sides(kind, n, its, dt):
+    """Right-hand sides as amplitude fields are: a few CG steps solve for most of them, and the later steps work on
+    what is left.  CG keeps those steps' digits (5e-16 to 2e-15 per solve against 80-bit arithmetic), so the bound
+    is that of rough right-hand sides."""
+    m = _mesh(n)
+    X, Y = np.meshgrid(np.arange(n[0]), np.arange(n[1]))
+    r = np.random.default_rng(45)
+    mode = (np.exp(2j * np.pi * X / n[0]) + 0.5 * np.exp(-4j * np.pi * Y / n[1])).ravel()
+    w = 0.5 * (1 - np.tanh((np.hypot(X - n[0] / 2, Y - n[1] / 2) - 0.2 * min(n)) / 1.5)).ravel()
+    noise = r.normal(size=mode.size) + 1j * r.normal(size=mode.size)
+    f = {"grain": 0.16 * (w * np.exp(0.03j * (X - Y)).ravel() + 1 - w), "mode+1e-4": mode + 1e-4 * noise,
+         "mode+1e-6": mode + 1e-6 * noise}[kind]
+    pairs = [(np.stack([f, 2 * f, 1j * f]), np.stack([f, -f, f[::-1]]))]
+    assert _worst([m], pairs, _pinv([m], pairs, its, dt=dt), its, dt=dt) <= TOL
+
+
+@pytest.mark.parametrize("mass", ["iter", "sep"])
+@pytest.mark.parametrize("its", [(1, 1), (2, 1), (1, 2), (2, 2)])
+@pytest.mark.parametrize("n", [(121, 25), (250, 234), (421, 400)])    # 2, 4 and 8 rows per wave
+def test_shapes_of_the_step_sequence(n, its, mass):
+    """Solves of one and two steps, whose first and last steps take other vectors than those between."""
+    m = [_mesh(n)]
+    pairs = _random(m, 46)
+    assert _worst(m, pairs, _pinv(m, pairs, its, mass), its, mass) <= TOL
+
+
+def test_large_meshes_in_a_batch():
+    """More regions than CUs whatever their rows: four rows per wave, uneven systems."""
+    m = [_mesh(n) for n in ((250, 234), (40, 28), (300, 260), (256, 512), (190, 310), (64, 64), (380, 220), (301, 299))]
+    pairs = _random(m, 47)
+    assert _worst(m, pairs, _pinv(m, pairs, (3, 5)), (3, 5)) <= TOL
 
 
 def test_step_on_the_static_scratch():
