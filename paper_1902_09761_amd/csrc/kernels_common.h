@@ -153,17 +153,16 @@ __device__ __forceinline__ void wave_sums(double (&v)[NV], F&& out) {
         if (idx + 64 * i < NV) out(idx + 64 * i, v[i]);
 }
 
-// Sum NV per-thread values over the workgroup of 4 waves; out(i, total of value i) is called by thread i.
-// lds >= 4*NV.
+// Sum NV per-thread values over the workgroup of 4 waves; out(i, total of value i) is called by thread i % 64: by
+// the first wave, so that a fence of thread 0 after it waits for what out stores (last_of_system; a wave waits for
+// its own stores).  lds >= 4*NV.
 template <int NV, typename F>
 __device__ __forceinline__ void block_totals(double (&v)[NV], double* lds, F&& out) {
     const int wv = threadIdx.x >> 6;
     wave_sums<NV>(v, [&](int i, double t) { lds[wv * NV + i] = t; });
     __syncthreads();
-    if (threadIdx.x < NV) {
-        const int i = threadIdx.x;
-        out(i, ((lds[i] + lds[NV + i]) + lds[2 * NV + i]) + lds[3 * NV + i]);
-    }
+    if (threadIdx.x < 64)
+        for (int i = threadIdx.x; i < NV; i += 64) out(i, ((lds[i] + lds[NV + i]) + lds[2 * NV + i]) + lds[3 * NV + i]);
     __syncthreads();
 }
 
