@@ -211,7 +211,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(const Sys* sys, con
     auto valid = [&](int i) { return x < nx && yb + 4 * i < ny; };
     auto node = [&](int i) { return s.off + (long long)(yb + 4 * i) * nx + x; };
     auto local = [&](int i) { return (yb + 4 * i) * kTX + x; };
-    const int xl = x == 0 ? nx - 1 : x - 1, xr = x == nx - 1 ? 0 : x + 1;
+    // of lanes beyond the mesh too (their results are not used): columns of the mesh
+    const int xl = x == 0 || x >= nx ? nx - 1 : x - 1, xr = x >= nx - 1 ? 0 : x + 1;
     // u <- f(M u, K u, T u) (K, T: only with WK, WT), u given at the thread's rows
     auto apply = [&](auto wk, auto wt, cx<T> (&u)[kSmallRows], auto&& f) {
         constexpr bool WK = decltype(wk)::value, WT = decltype(wt)::value;

@@ -71,6 +71,13 @@ def test_one_workgroup_per_system(precision, tol, n, its, mass):
     assert _worst(m, pairs, _pinv(m, pairs, its, mass, precision=precision), its, mass) <= tol
 
 
+@pytest.mark.parametrize("n", [(40, 64), (63, 64), (4, 64)])
+def test_one_workgroup_narrow_and_tall(n):
+    m = [_mesh(n)]
+    pairs = _random(m, 48)
+    assert _worst(m, pairs, _pinv(m, pairs, (3, 5)), (3, 5)) <= TOL
+
+
 def test_batch_of_uneven_meshes():
     m = [_mesh(n) for n in ((40, 28), (64, 64), (7, 90), (200, 33))]
     pairs = _random(m, 42)
