@@ -292,7 +292,8 @@ int apfc_autotune(apfc_ctx* ctx, void* stream, int* chosen_tile_rows);
  * rows / threads: 0: 128x32 / 512, 1: 64x32 / 256, 2: 64x64 / 512, 3: 128x36 / 512, 4: 128x64 / 1024,
  * 5: 256x32 / 1024; a Chebyshev stage keeps two LDS copies of its region in FP32 and one in FP64, the
  * separable mass stage one; taller regions recompute less halo, smaller ones leave room for more
- * workgroups per CU).  Needs the workspace.  The 3D bricks of the separable mass inverse and of the
+ * workgroups per CU).  Small 2D meshes, whose preconditioner runs in one launch on regions of its own, use
+ * precond_region only for Krylov indices above 8 (restart > 9).  Needs the workspace.  The 3D bricks of the separable mass inverse and of the
  * Chebyshev L solves (64 x 8 nodes per plane, 8 or 16 planes) are chosen at creation, not here. */
 int apfc_set_tiles(apfc_ctx* ctx, int tile_rows, int precond_region);
 int apfc_get_tiles(const apfc_ctx* ctx, int* tile_rows, int* precond_region);

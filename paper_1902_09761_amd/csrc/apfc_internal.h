@@ -117,6 +117,7 @@ struct Dev {
     int maxn[3] = {1, 1, 1};         // largest mesh sizes over the systems
     long long NT = 0;                // half-vector length (complex values)
     Terms terms{};
+    bool cheb_stages = false;        // 2D Chebyshev preconditioner in its three launches whatever the mesh
     Probe* probe = nullptr;
 };
 

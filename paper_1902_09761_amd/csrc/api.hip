@@ -1871,7 +1871,8 @@ int apfc_autotune(apfc_ctx* c, void* stream, int* chosen) {
     c->TY = cand[bi];
     build_tiles(*c, c->TY, c->tiles);
     if (int rc = upload_tables(*c); rc) return rc;
-    // region shape of the fused 2D Chebyshev preconditioner
+    // region shape of the fused 2D Chebyshev preconditioner, by its three launches: small meshes take one launch
+    // instead (kernels_cheb2d.hip), but not for Krylov indices above 8, and those take the shape found here
     if (c->solver.inner_kind == APFC_INNER_CHEB && c->dim == 2) {
         float best_sh[kChebShapes];
         for (int sh = 0; sh < kChebShapes; ++sh) best_sh[sh] = 1e30f;
@@ -1883,6 +1884,7 @@ int apfc_autotune(apfc_ctx* c, void* stream, int* chosen) {
                 build_ctiles(*c);
                 if (int rc = upload_tables(*c); rc) return rc;
                 Dev d = c->dev();
+                d.cheb_stages = true;
                 d.probe = nullptr;
                 auto body = [&]() {
                     if (c->mixed)

@@ -561,7 +561,7 @@ void launch_precond_cheb(const Dev& d, int shape, const CTile* ctiles, int nctil
                          const VIn<T>& vin, const int* mask, hipStream_t st) {
     int halo_all = 0;
     // with many basis vectors the halo's share of their loads outweighs the saved launches
-    const dim3 all = vin.nv <= 8 ? cheb_all_grid(d, mass_iters, diff_iters, mass_sep, halo_all) : dim3(0);
+    const dim3 all = vin.nv <= 8 && !d.cheb_stages ? cheb_all_grid(d, mass_iters, diff_iters, mass_sep, halo_all) : dim3(0);
     if (all.x > 0) {
         const double c = sizeof(cx<T>), in = c * (vin.src ? 2 + vin.nv : 1);
         ProbeScope ps(d, KID_CHEB, st, (double)d.NT * 2.0 * (in + c), mask, true);

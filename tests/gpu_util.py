@@ -43,3 +43,13 @@ def eq_of(k):
     """dB -> relaxed amplitude of every amplitude (one value per shell of |k_j|; FCC has two)."""
     from oracle.apfc_oracle import equilibrium_amplitudes
     return lambda dB: equilibrium_amplitudes(BulkEnergy(k, Params.from_dB(dB)))
+
+
+def kernels_of(fn):
+    """{kernel name: launches} of the GPU kernels that fn launches."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    return {e.key: e.count for e in p.key_averages() if "apfc::" in e.key}

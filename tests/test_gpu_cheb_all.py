@@ -1,11 +1,13 @@
 """The 2D Chebyshev preconditioner in one launch (meshes whose regions all fit on the chip at once) and, just
 above that size, in three, against the oracle's four steps, element by element.  Needs an MI355X."""
+import re
+
 import numpy as np
 import pytest
 
 from oracle.apfc_oracle import tri_k
 from paper_1902_09761_amd import apfc, inputs
-from tests.gpu_util import H_TRI, from_dev, oracle_for, rel_l2, solver_for, to_dev
+from tests.gpu_util import H_TRI, from_dev, kernels_of, oracle_for, rel_l2, solver_for, to_dev
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -70,3 +72,18 @@ def test_forms_the_basis_vectors():
         _, ref = o.step(ref, 1.0)
         s.step([et], [zt], 1.0)
     assert rel_l2(from_dev(et), ref) <= 1e-9
+
+
+def _shapes(names):
+    """Region shapes (columns, rows) of the three-launch kernel among kernel names."""
+    return {tuple(map(int, m)) for n in names for m in re.findall(r"k_cheb2d<\w+, \d+, (\d+), (\d+),", n)}
+
+
+SHAPES = [(128, 32), (64, 32), (64, 64), (128, 36), (128, 64), (256, 32)]
+
+
+def test_autotune_times_the_region_shapes():
+    """On a mesh that takes one launch the search still runs every region shape: Krylov indices above 8 use it."""
+    s = solver_for([_mesh((96, 80))], apfc.APFC_TRI2D, [0.02], inner_kind=apfc.APFC_INNER_CHEB, mass_iters=3, diff_iters=3,
+                   mass_kind=apfc.APFC_MASS_SEPARABLE)
+    assert _shapes(kernels_of(s.autotune)) == set(SHAPES)
