@@ -87,3 +87,13 @@ def test_autotune_times_the_region_shapes():
     s = solver_for([_mesh((96, 80))], apfc.APFC_TRI2D, [0.02], inner_kind=apfc.APFC_INNER_CHEB, mass_iters=3, diff_iters=3,
                    mass_kind=apfc.APFC_MASS_SEPARABLE)
     assert _shapes(kernels_of(s.autotune)) == set(SHAPES)
+
+
+@pytest.mark.parametrize("precision,tol", [(apfc.APFC_FP64, 1e-12), (apfc.APFC_MIXED, 2e-5)])
+@pytest.mark.parametrize("region,taps", [(0, 1), (1, 2), (2, 4), (3, 3), (4, 1), (5, 2), (0, 3), (4, 4)])
+def test_three_launches_with_the_separable_stage(region, taps, precision, tol):
+    """Every region shape and tap count on a mesh of more regions than CUs, and that these kernels ran."""
+    worst = []
+    names = kernels_of(lambda: worst.append(_worst([_mesh((331, 257))], precision, (taps, 3), True, region=region)))
+    assert _shapes(names) == {SHAPES[region]} and not any("k_cheb2d_all" in n for n in names)
+    assert worst[0] <= tol

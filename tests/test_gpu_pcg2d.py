@@ -5,7 +5,7 @@ import pytest
 
 from oracle.apfc_oracle import tri_k
 from paper_1902_09761_amd import apfc, inputs
-from tests.gpu_util import H_TRI, from_dev, oracle_for, solver_for, to_dev
+from tests.gpu_util import H_TRI, from_dev, kernels_of, oracle_for, solver_for, to_dev
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -134,6 +134,17 @@ def test_large_meshes_in_a_batch():
     m = [_mesh(n) for n in ((250, 234), (40, 28), (300, 260), (256, 512), (190, 310), (64, 64), (380, 220), (301, 299))]
     pairs = _random(m, 47)
     assert _worst(m, pairs, _pinv(m, pairs, (3, 5)), (3, 5)) <= TOL
+
+
+@pytest.mark.parametrize("n,its,mass", [((96, 80), (6, 7), "iter"), ((70, 65), (5, 6), "iter"), ((130, 70), (3, 8), "sep")])
+def test_longer_solves(n, its, mass):
+    """More than five iterations per solve: two launches per step."""
+    m = [_mesh(n)]
+    pairs = _random(m, 49)
+    got = []
+    names = kernels_of(lambda: got.append(_pinv(m, pairs, its, mass)))
+    assert any("k_cg_spmv<2" in k for k in names) and not any("k_pcg" in k for k in names)
+    assert _worst(m, pairs, got[0], its, mass) <= TOL
 
 
 def test_step_on_the_static_scratch():
