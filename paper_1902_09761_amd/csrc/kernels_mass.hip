@@ -171,9 +171,23 @@ constexpr int kLineB = 8, kLineMax = 64 * kLineB - 2 * kLineHalo;
 
 __device__ __forceinline__ int line_segs(int n) { return (n + kLineMax - 1) / kLineMax; }
 
-__global__ __launch_bounds__(kBlock) void k_zeta_x(const Sys* sys, const zd* __restrict__ eta, zd* __restrict__ zeta) {
+// The system of this workgroup, which of the system's workgroups it is and how many there are: row blockIdx.y of the
+// grid, or with tiles the one of tile blockIdx.x (launch_zeta).
+struct ZetaBlock {
+    const Sys* s;
+    int b, n;
+    __device__ ZetaBlock(const Sys* sys, const Tile* tiles) {
+        s = sys + (tiles ? tiles[blockIdx.x].sys : (int)blockIdx.y);
+        b = (int)blockIdx.x - (tiles ? s->tbeg : 0);
+        n = tiles ? s->tend - s->tbeg : (int)gridDim.x;
+    }
+};
+
+__global__ __launch_bounds__(kBlock) void k_zeta_x(const Sys* sys, const Tile* tiles, const zd* __restrict__ eta,
+                                                  zd* __restrict__ zeta) {
     __shared__ zd buf[kBlock / 64][64 * (kLineB + 1)];
-    const Sys* s = sys + blockIdx.y;
+    const ZetaBlock blk(sys, tiles);
+    const Sys* s = blk.s;
     const int nx = s->nx, segs = line_segs(nx), nout = (nx + segs - 1) / segs;
     const int gw = (nout + 2 * kLineHalo + kLineB - 1) / kLineB, gpw = 64 / gw, gn = gw * kLineB;
     const long long off = s->off, items = (long long)s->ny * s->nz * segs;
@@ -184,7 +198,7 @@ __global__ __launch_bounds__(kBlock) void k_zeta_x(const Sys* sys, const zd* __r
     // no neighbour inside the segment: the block's own end stands in, kLineHalo nodes from any output
     const bool first = lane % gw == 0, last = lane % gw == gw - 1 || lane == 63;
     const double rb = kRho * kRho, rho8 = rb * rb * rb * rb;
-    for (long long it0 = (long long)blockIdx.x * 4 * gpw; it0 < items; it0 += (long long)gridDim.x * 4 * gpw) {
+    for (long long it0 = (long long)blk.b * 4 * gpw; it0 < items; it0 += (long long)blk.n * 4 * gpw) {
         auto node = [&](int e, bool& out) -> long long {   // node of element e, -1: none; out: an output node
             const int g = e / gn, p = e - g * gn;
             const long long item = it0 + (long long)wv * gpw + g;
@@ -250,92 +264,101 @@ __global__ __launch_bounds__(kBlock) void k_zeta_x(const Sys* sys, const zd* __r
 constexpr int kLineSeg = 32;
 
 template <int DIR>
-__global__ __launch_bounds__(kBlock) void k_zeta_line(const Sys* sys, const zd* __restrict__ eta, zd* __restrict__ zeta) {
-    const Sys* s = sys + blockIdx.y;
+__global__ __launch_bounds__(kBlock) void k_zeta_line(const Sys* sys, const Tile* tiles, const zd* __restrict__ eta,
+                                                     zd* __restrict__ zeta) {
+    const ZetaBlock blk(sys, tiles);
+    const Sys* s = blk.s;
     const int n = DIR == 1 ? s->ny : s->nz, nx = s->nx;
     const int lines = DIR == 1 ? nx * s->nz : nx * s->ny, segs = (n + kLineSeg - 1) / kLineSeg;
-    const long long t = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= (long long)lines * segs) return;
-    const int seg = (int)(t / lines), line = (int)(t - (long long)seg * lines);
     const long long stride = DIR == 1 ? nx : (long long)nx * s->ny;
-    const long long base = s->off + (DIR == 1 ? (long long)(line / nx) * nx * s->ny + line % nx : (long long)line);
     const double a = -6.0 / (s->h * s->h) * kLineNorm, b = 6.0 * s->kv[DIR] / s->h * kLineNorm;
-    const zd* e = eta + base;
-    zd* z = zeta + base;
     auto wrap = [&](int p) {
         p %= n;
         return p < 0 ? p + n : p;
     };
     auto src = [&](zd l, zd c, zd r) { return a * ((c + c) - (l + r)) + b * mul_i(r - l); };
-    const int s0 = seg * kLineSeg;
-    zd f[kLineSeg], v{0.0, 0.0};
-    {
-        int p = wrap(s0 - kLineHalo - 1);
-        auto next = [&]() {
+    for (long long t = (long long)blk.b * kBlock + threadIdx.x; t < (long long)lines * segs; t += (long long)blk.n * kBlock) {
+        const int seg = (int)(t / lines), line = (int)(t - (long long)seg * lines);
+        const long long base = s->off + (DIR == 1 ? (long long)(line / nx) * nx * s->ny + line % nx : (long long)line);
+        const zd* e = eta + base;
+        zd* z = zeta + base;
+        const int s0 = seg * kLineSeg;
+        zd f[kLineSeg], v{0.0, 0.0};
+        {
+            int p = wrap(s0 - kLineHalo - 1);
+            auto next = [&]() {
+                const zd u = e[p * stride];
+                p = p + 1 == n ? 0 : p + 1;
+                return u;
+            };
+            zd l = next(), c = next();
+#pragma unroll 8
+            for (int k = 0; k < kLineHalo; ++k) {
+                const zd r = next();
+                v = src(l, c, r) + kRho * v;
+                l = c;
+                c = r;
+            }
+#pragma unroll
+            for (int k = 0; k < kLineSeg; ++k) {
+                const zd r = next();
+                v = src(l, c, r) + kRho * v;
+                f[k] = v;
+                l = c;
+                c = r;
+            }
+        }
+        v = zd{0.0, 0.0};
+        int p = wrap(s0 + kLineSeg + kLineHalo);
+        auto prev = [&]() {
             const zd u = e[p * stride];
-            p = p + 1 == n ? 0 : p + 1;
+            p = p == 0 ? n - 1 : p - 1;
             return u;
         };
-        zd l = next(), c = next();
+        zd r = prev(), c = prev();
 #pragma unroll 8
         for (int k = 0; k < kLineHalo; ++k) {
-            const zd r = next();
+            const zd l = prev();
             v = src(l, c, r) + kRho * v;
-            l = c;
-            c = r;
+            r = c;
+            c = l;
         }
 #pragma unroll
-        for (int k = 0; k < kLineSeg; ++k) {
-            const zd r = next();
-            v = src(l, c, r) + kRho * v;
-            f[k] = v;
-            l = c;
-            c = r;
+        for (int k = kLineSeg - 1; k >= 0; --k) {
+            const zd l = prev();
+            const zd y = src(l, c, r);
+            v = y + kRho * v;
+            if (s0 + k < n) {
+                const long long o = (s0 + k) * stride;
+                z[o] = z[o] + ((f[k] + v) - y);
+            }
+            r = c;
+            c = l;
         }
-    }
-    v = zd{0.0, 0.0};
-    int p = wrap(s0 + kLineSeg + kLineHalo);
-    auto prev = [&]() {
-        const zd u = e[p * stride];
-        p = p == 0 ? n - 1 : p - 1;
-        return u;
-    };
-    zd r = prev(), c = prev();
-#pragma unroll 8
-    for (int k = 0; k < kLineHalo; ++k) {
-        const zd l = prev();
-        v = src(l, c, r) + kRho * v;
-        r = c;
-        c = l;
-    }
-#pragma unroll
-    for (int k = kLineSeg - 1; k >= 0; --k) {
-        const zd l = prev();
-        const zd y = src(l, c, r);
-        v = y + kRho * v;
-        if (s0 + k < n) {
-            const long long o = (s0 + k) * stride;
-            z[o] = z[o] + ((f[k] + v) - y);
-        }
-        r = c;
-        c = l;
     }
 }
 
+// Grid: the workgroups that the largest mesh needs for every system, where the meshes are of like size; else the stencil
+// tiles, each system's sharing out its lines (a few more workgroups than lines: apfc_energy_grad of one
+// 90 x 96 x 77 x 6 in 385 us instead of 356).  With 1024^2 and 1023 meshes of 16^2, x 3, the former is nearly all empty
+// workgroups (apfc_energy 4903 us, by tiles 268); the line lies where half of the larger grid would be empty.
 void launch_zeta(const Dev& d, const zd* eta, zd* zeta, hipStream_t st) {
     const int* mx = d.maxn;
-    auto blocks = [](long long threads) { return (unsigned)((threads + kBlock - 1) / kBlock); };
+    const Tile* tiles = (double)mx[0] * mx[1] * mx[2] * d.S > 2.0 * (double)d.NT ? d.tiles : nullptr;
+    auto grid = [&](long long n) { return tiles ? dim3(d.ntiles) : dim3((unsigned)n, d.S); };
     const int segs = (mx[0] + kLineMax - 1) / kLineMax, nout = (mx[0] + segs - 1) / segs;
     const int gpw = 64 / ((nout + 2 * kLineHalo + kLineB - 1) / kLineB);
     const long long rows = (long long)mx[1] * mx[2] * segs;
-    hipLaunchKernelGGL(k_zeta_x, dim3((unsigned)std::min<long long>((rows + 4 * gpw - 1) / (4 * gpw), 1 << 20), d.S),
-                       dim3(kBlock), 0, st, d.sys, eta, zeta);
-    auto segn = [](int n) { return (long long)(n + kLineSeg - 1) / kLineSeg; };
-    hipLaunchKernelGGL(k_zeta_line<1>, dim3(blocks((long long)mx[0] * mx[2] * segn(mx[1])), d.S), dim3(kBlock), 0, st,
-                       d.sys, eta, zeta);
+    hipLaunchKernelGGL(k_zeta_x, grid(std::min<long long>((rows + 4 * gpw - 1) / (4 * gpw), 1 << 20)), dim3(kBlock), 0, st,
+                       d.sys, tiles, eta, zeta);
+    auto line_blocks = [&](int lines, int n) {
+        return ((long long)lines * ((n + kLineSeg - 1) / kLineSeg) + kBlock - 1) / kBlock;
+    };
+    hipLaunchKernelGGL(k_zeta_line<1>, grid(line_blocks(mx[0] * mx[2], mx[1])), dim3(kBlock), 0, st, d.sys, tiles, eta,
+                       zeta);
     if (d.dim == 3)
-        hipLaunchKernelGGL(k_zeta_line<2>, dim3(blocks((long long)mx[0] * mx[1] * segn(mx[2])), d.S), dim3(kBlock), 0,
-                           st, d.sys, eta, zeta);
+        hipLaunchKernelGGL(k_zeta_line<2>, grid(line_blocks(mx[0] * mx[1], mx[2])), dim3(kBlock), 0, st, d.sys, tiles,
+                           eta, zeta);
 }
 
 }  // namespace apfc

@@ -54,6 +54,46 @@ def test_zeta_energy_gradient_of_an_uneven_batch():
         assert abs(ddB[b] - o.energy_ddB(etas[b])) <= 1e-12 * abs(o.energy_ddB(etas[b]))
 
 
+@pytest.mark.parametrize("rows", [4, 32])
+@pytest.mark.parametrize("ns", [((200, 150), (6, 5), (4, 70), (5, 4), (11, 9)), ((70, 4, 8), (4, 4, 4), (5, 9, 4), (4, 6, 5))])
+def test_zeta_of_one_large_and_several_small_meshes(ns, rows):
+    """Meshes of very different sizes share out each system's lines over its tiles, also where tiles are fewer than
+    the workgroups that the lines would fill (70 x 4 x 8 by tiles of 32 rows)."""
+    meshes = [_mesh(n) for n in ns]
+    kind, k = (apfc.APFC_TRI2D, tri_k()) if len(ns[0]) == 2 else (apfc.APFC_BCC3D, bcc_k())
+    rng = np.random.default_rng(19)
+    etas = [rng.normal(size=(len(k), m.N)) + 1j * rng.normal(size=(len(k), m.N)) for m in meshes]
+    s = solver_for(meshes, kind, [0.02] * len(meshes))
+    s.set_tiles(rows)
+    zs = [torch.full((len(k), 2, m.N), float("nan"), dtype=torch.float64, device="cuda") for m in meshes]
+    s.init_zeta([to_dev(e) for e in etas], zs)
+    for m, e, z in zip(meshes, etas, zs):
+        assert rel_l2(from_dev(z), oracle_for(m, k, 0.02).zeta_of(e)) <= 1e-13
+
+
+def test_time_of_a_batch_follows_its_nodes():
+    """The launches of one 1024^2 and 511 meshes of 16^2 (an eighth more nodes) take at most four times as long as those
+    of the large one alone; as many workgroups for a small mesh as for the large one made it thirty."""
+    from torch.profiler import ProfilerActivity, profile
+    large, small = _mesh((1024, 1024)), _mesh((16, 16))
+
+    def best(meshes):
+        s = solver_for(meshes, apfc.APFC_TRI2D, [0.02] * len(meshes))
+        etas = [torch.zeros((3, 2, m.N), dtype=torch.float64, device="cuda") for m in meshes]
+        zs = [torch.zeros_like(e) for e in etas]
+        t = []
+        for _ in range(3):
+            with profile(activities=[ProfilerActivity.CUDA]) as p:
+                s.init_zeta(etas, zs)
+                torch.cuda.synchronize()
+            t.append(sum(e.device_time_total for e in p.key_averages() if "k_zeta" in e.key))
+        return min(t)
+
+    alone, batch = best([large]), best([large] + [small] * 511)
+    print("1024^2:", alone, "with 511 of 16^2:", batch, "us")
+    assert 0 < batch <= 4 * alone
+
+
 def test_fcc_energy_gradient():
     """Seven amplitudes: the nodal part's eight-slot instance, rows shared by more tiles than a tile has rows."""
     mesh = _mesh((9, 6, 11))
