@@ -45,11 +45,35 @@ def eq_of(k):
     return lambda dB: equilibrium_amplitudes(BulkEnergy(k, Params.from_dB(dB)))
 
 
-def kernels_of(fn):
-    """{kernel name: launches} of the GPU kernels that fn launches."""
+def kernel_times(fn):
+    """{kernel name: us on the GPU} of this library's kernels that fn launches, by torch's profiler.  It drops kernels
+    whose time stamps lie outside the profile, hence the pauses around fn."""
+    import time
+
     import torch
     from torch.profiler import ProfilerActivity, profile
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
-        fn()
-        torch.cuda.synchronize()
-    return {e.key: e.count for e in p.key_averages() if "apfc::" in e.key}
+    for _ in range(5):
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            time.sleep(0.05)
+            fn()
+            torch.cuda.synchronize()
+            time.sleep(0.05)
+        out = {e.key: e.device_time_total for e in p.key_averages() if "apfc::" in e.key}
+        if out:
+            return out
+    raise RuntimeError("the profiler recorded no kernel")
+
+
+def families_of_a_step(s, meshes, J=3):
+    """{kernel family: launches} of one step of solver s from nearly uniform amplitudes, by the library's probe."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(7)
+    etas = [0.2 + 0.01 * torch.rand((J, 2, m.N), dtype=torch.float64, device="cuda", generator=g) for m in meshes]
+    zetas = [torch.zeros_like(e) for e in etas]
+    s.init_zeta(etas, zetas)
+    s.probe_enable("all", 1000)
+    s.step(etas, zetas, 1.0)
+    torch.cuda.synchronize()
+    out = {k: s.probe_read_kernel(k)[3] for k in ("cheb", "apply", "pcg_spmv", "pcg_update", "mass", "mg")}
+    s.probe_enable(None, 1)
+    return out

@@ -5,7 +5,7 @@ import pytest
 
 from oracle.apfc_oracle import bcc_k, fcc_k, tri_k
 from paper_1902_09761_amd import apfc, inputs
-from tests.gpu_util import H_TRI, from_dev, oracle_for, rel_l2, solver_for, to_dev
+from tests.gpu_util import H_TRI, from_dev, kernel_times, oracle_for, rel_l2, solver_for, to_dev
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -74,20 +74,14 @@ def test_zeta_of_one_large_and_several_small_meshes(ns, rows):
 def test_time_of_a_batch_follows_its_nodes():
     """The launches of one 1024^2 and 511 meshes of 16^2 (an eighth more nodes) take at most four times as long as those
     of the large one alone; as many workgroups for a small mesh as for the large one made it thirty."""
-    from torch.profiler import ProfilerActivity, profile
     large, small = _mesh((1024, 1024)), _mesh((16, 16))
 
     def best(meshes):
         s = solver_for(meshes, apfc.APFC_TRI2D, [0.02] * len(meshes))
         etas = [torch.zeros((3, 2, m.N), dtype=torch.float64, device="cuda") for m in meshes]
         zs = [torch.zeros_like(e) for e in etas]
-        t = []
-        for _ in range(3):
-            with profile(activities=[ProfilerActivity.CUDA]) as p:
-                s.init_zeta(etas, zs)
-                torch.cuda.synchronize()
-            t.append(sum(e.device_time_total for e in p.key_averages() if "k_zeta" in e.key))
-        return min(t)
+        return min(sum(us for k, us in kernel_times(lambda: s.init_zeta(etas, zs)).items() if "k_zeta" in k)
+                   for _ in range(3))
 
     alone, batch = best([large]), best([large] + [small] * 511)
     print("1024^2:", alone, "with 511 of 16^2:", batch, "us")
