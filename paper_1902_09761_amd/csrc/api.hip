@@ -133,6 +133,7 @@ struct apfc_ctx {
     size_t max_ctiles = 0;
     std::vector<CTile> rtiles;         // regions of the fused 2D Jacobi-PCG preconditioner (empty: not used)
     int pcg_rows = 0;                  // their rows per wave (kPcgRows)
+    bool pcg_small = false;            // 2D Jacobi-PCG by one workgroup per system
     long long NT = 0, NI = 0;
     int maxn[3] = {1, 1, 1};           // largest mesh sizes over the systems
     int TY = 16;
@@ -479,10 +480,29 @@ void build_ctiles(apfc_ctx& c) {
     }
 }
 
-// Regions of the 2D Jacobi-PCG preconditioner with one launch per step: FP64 and up to kPcgMax iterations per inner solve,
-// where it was compared with the two launches per step that sum <p, OP p> in a pass of its own (kernels_pcg2d.hip).  In
+// 2D Jacobi-PCG on many meshes of few rows: the launches per half-step share the chip by 16-row tiles, while one workgroup
+// per system (launch_precond_pcg_small, the same bits) takes 2.5 to 4.5 us per CG step and round of one workgroup per CU
+// however small the mesh, and the regions of launch_precond_pcg2d are 16 rows or more.  P^{-1} by the launches over
+// P^{-1} by workgroups, FP64, 3 + 5 + 5 steps:
+//   up to three systems per CU       4^2 1.2 to 2.8,  16^2 1.5 to 2.8,  64^2 2.3 to 3.7
+//   4 to 32 systems per CU           4^2 0.86 to 0.44, 12^2 1.09 to 0.81, 16^2 1.28 to 1.00, 20^2 1.9 to 1.7
+// with 1 + 1 + 1 steps 16^2 0.96 to 0.69, 20^2 1.17 to 1.00; FP32 alike.  By regions: 768 systems of 4^2 1.03,
+// 3072 of 66 x 4 0.72, of 16^2 1.15, of 66 x 20 2.3.
+bool many_tiny(const apfc_ctx& c) {
+    long long tiles = 0, rows = 0;
+    for (const Sys& y : c.sys) {
+        tiles += (y.ny + 15) / 16;
+        rows += y.ny;
+    }
+    const int steps = (c.solver.mass_kind == APFC_MASS_SEPARABLE ? 0 : c.solver.mass_iters) + 2 * c.solver.diff_iters;
+    return c.S > 3 * device_cus() && 2 * tiles < 3LL * c.S && (rows < 16LL * c.S || steps < 10);
+}
+
+// The 2D Jacobi-PCG preconditioner's kernels, and the regions of launch_precond_pcg2d (one launch per step): FP64 and up
+// to kPcgMax iterations per inner solve, where it was compared with the two launches per step that sum <p, OP p> in a pass of its own (kernels_pcg2d.hip).  In
 // FP32 storage with long restarts the rounding of z decides how far below rtol a solve ends, and CG's own rounding is
-// kept there.  Meshes of at most 64 x 64 nodes go to launch_precond_pcg_small.
+// kept there.  Meshes of at most 64 x 64 nodes go to launch_precond_pcg_small, batches of
+// many tiny ones to the launches per half-step.
 // Rows per wave (kPcgRows): the fewest that leave at most one region per CU, where latency counts and a taller region
 // takes longer (P^{-1} of 180 x 170 x 3 by 2, 4, 8 rows: 104, 120, 150 us; 320^2 x 3: 150, 143, 178; 512^2 x 3: 295, 260,
 // 237).  Where none does, 4 rows (1024^2 x 3: 1237, 842, 840 us; 24 meshes of 250 x 234 x 3: 1228, 1166, 1267), or 8 on
@@ -490,11 +510,13 @@ void build_ctiles(apfc_ctx& c) {
 // 2048^2 x 3: 5137, 4090).
 // The region table lies in the work vector pc[5] and the partials in apart, which the two-launch path uses otherwise.
 CTile* rtile_table(const apfc_ctx& c) { return (CTile*)c.pc[5]; }
-void build_rtiles(apfc_ctx& c) {
+void choose_pcg(apfc_ctx& c) {
     c.rtiles.clear();
     const apfc_params& p = c.solver;
-    if (c.dim != 2 || p.inner_kind != APFC_INNER_PCG || p.diff_iters > kPcgMax ||
-        (p.mass_kind != APFC_MASS_SEPARABLE && p.mass_iters > kPcgMax) || c.mixed || (c.maxn[0] <= kTX && c.maxn[1] <= kTX))
+    c.pcg_small = false;
+    if (c.dim != 2 || p.inner_kind != APFC_INNER_PCG || many_tiny(c)) return;
+    c.pcg_small = c.maxn[0] <= kTX && c.maxn[1] <= kTX;
+    if (c.pcg_small || p.diff_iters > kPcgMax || (p.mass_kind != APFC_MASS_SEPARABLE && p.mass_iters > kPcgMax) || c.mixed)
         return;
     const int IX = kTX - 2 * kPcgHalo;
     auto interior = [](int rows) { return rows * (kPcgThreads / 64) - 2 * kPcgHalo; };
@@ -985,7 +1007,7 @@ int apfc_create_batch(int count, const apfc_mesh* meshes, const apfc_lattice* la
     c->TY = 16;
     build_tiles(*c, c->TY, c->tiles);
     set_dt_scalars(*c, 1.0);
-    build_rtiles(*c);
+    choose_pcg(*c);
     if (params[0].inner_kind == APFC_INNER_CHEB && dim == 2) {
         for (int sh = 0; sh < kChebShapes; ++sh) {
             c->cheb_shape = sh;
@@ -1165,7 +1187,7 @@ void precond(apfc_ctx* c, const Dev& d, const cx<T>* v, cx<T>* z, const int* mas
     else if (c->solver.inner_kind == APFC_INNER_CHEB)
         launch_precond_cheb_unfused<T>(d, v, z, pc[0], pc[1], pc[2], pc[3], pc[4], c->solver.mass_iters,
                                        c->solver.diff_iters, sep, mask, st);
-    else if (c->dim == 2 && c->maxn[0] <= kTX && c->maxn[1] <= kTX)
+    else if (c->pcg_small)
         launch_precond_pcg_small<T>(d, v, z, pc[0], pc[1], c->solver.mass_iters, c->solver.diff_iters, sep, mask, st);
     else if (std::is_same_v<T, double> && !c->rtiles.empty()) {
         if constexpr (std::is_same_v<T, double>)

@@ -88,6 +88,24 @@ def test_one_workgroup_narrow_and_tall(n):
     assert _worst(m, pairs, _pinv(m, pairs, (3, 5)), (3, 5)) <= TOL
 
 
+@pytest.mark.parametrize("n,count,its,small", [
+    ((8, 8), 256, (3, 5), True),       # three systems per CU
+    ((8, 8), 300, (3, 5), False), ((4, 5), 400, (1, 1), False), ((16, 16), 300, (1, 1), False),
+    ((16, 16), 300, (3, 5), True), ((7, 17), 300, (1, 1), True),
+    ((66, 5), 300, (3, 5), False),
+])
+@pytest.mark.parametrize("precision,tol", [(apfc.APFC_FP64, TOL), (apfc.APFC_MIXED, 2e-5)])
+def test_many_tiny_meshes(n, count, its, small, precision, tol):
+    """One workgroup per system up to three of them per CU and where a mesh has enough rows and steps; else launches
+    over all of them."""
+    m = [_mesh(n)] * count
+    pairs = (_random(m[:4], 50) * count)[:count]
+    assert _half_step_launches(m, its, precision=precision) != small
+    got = _pinv(m, pairs, its, precision=precision)
+    for q in (0, count - 2):
+        assert _worst(m[:2], pairs[q:q + 2], got[q:q + 2], its) <= tol
+
+
 def test_batch_of_uneven_meshes():
     m = [_mesh(n) for n in ((40, 28), (64, 64), (7, 90), (200, 33))]
     pairs = _random(m, 42)
