@@ -115,6 +115,7 @@ struct Dev {
     int nmtiles = 0, mbz = kBrickZShallow;   // brick depth in planes (3D)
     int ntiles = 0, nchunks = 0, S = 0, TY = 16, J = 0, count = 0, dim = 2;
     int maxn[3] = {1, 1, 1};         // largest mesh sizes over the systems
+    int cus = 256;                   // CUs of the device
     long long NT = 0;                // half-vector length (complex values)
     Terms terms{};
     bool cheb_stages = false;        // 2D Chebyshev preconditioner in its three launches whatever the mesh

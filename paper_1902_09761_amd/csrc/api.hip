@@ -136,6 +136,7 @@ struct apfc_ctx {
     bool pcg_small = false;            // 2D Jacobi-PCG by one workgroup per system
     long long NT = 0, NI = 0;
     int maxn[3] = {1, 1, 1};           // largest mesh sizes over the systems
+    int cus = 256;                     // CUs of the device
     int TY = 16;
     int max_tiles = 0;
     double dt = -1.0;
@@ -221,6 +222,7 @@ struct apfc_ctx {
         d.count = count;
         d.dim = dim;
         for (int q = 0; q < 3; ++q) d.maxn[q] = maxn[q];
+        d.cus = cus;
         d.NT = NT;
         d.terms = terms;
         d.probe = probe.target != KID_NONE ? &probe : nullptr;
@@ -450,9 +452,8 @@ void build_mtiles(apfc_ctx& c) {
         }
         return n;
     };
-    const int cus = device_cus();
     auto cost = [&](int bz) {
-        const long long slots = (long long)cus * std::max(1, brick_occupancy(bz, c.mixed));
+        const long long slots = (long long)c.cus * std::max(1, brick_occupancy(bz, c.mixed));
         return (count(bz) + slots - 1) / slots * (bz + 2);
     };
     c.mbz = c.dim == 3 && cost(kBrickZDeep) < cost(kBrickZShallow) ? kBrickZDeep : kBrickZShallow;
@@ -495,7 +496,7 @@ bool many_tiny(const apfc_ctx& c) {
         rows += y.ny;
     }
     const int steps = (c.solver.mass_kind == APFC_MASS_SEPARABLE ? 0 : c.solver.mass_iters) + 2 * c.solver.diff_iters;
-    return c.S > 3 * device_cus() && 2 * tiles < 3LL * c.S && (rows < 16LL * c.S || steps < 10);
+    return c.S > 3 * c.cus && 2 * tiles < 3LL * c.S && (rows < 16LL * c.S || steps < 10);
 }
 
 // The 2D Jacobi-PCG preconditioner's kernels, and the regions of launch_precond_pcg2d (one launch per step): FP64 and up
@@ -526,10 +527,9 @@ void choose_pcg(apfc_ctx& c) {
         for (const Sys& y : c.sys) n += (long long)((y.nx + IX - 1) / IX) * ((y.ny + IY - 1) / IY);
         return n;
     };
-    const int cus = device_cus();
     c.pcg_rows = c.NT > (1LL << 20) * c.S ? kPcgRows[2] : kPcgRows[1];
     for (int rows : kPcgRows)
-        if (count(rows) <= cus) {
+        if (count(rows) <= c.cus) {
             c.pcg_rows = rows;
             break;
         }
@@ -918,6 +918,7 @@ int apfc_create_batch(int count, const apfc_mesh* meshes, const apfc_lattice* la
     }
     if (int rc = check_lattice(*lattice, dim); rc) return rc;
     auto c = new apfc_ctx();
+    c->cus = device_cus();
     c->count = count;
     c->J = lattice->J;
     c->dim = dim;

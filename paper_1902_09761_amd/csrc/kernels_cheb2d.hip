@@ -367,13 +367,14 @@ __global__ __launch_bounds__(NTH, sizeof(T) == 4 ? 4 : 2) void k_cheb2d(
 }
 
 // ------------------------------------------------------------------------------------------
-// The three stages in one launch, for meshes whose regions all fit on the chip at once (kChebAllRegions): a
+// The three stages in one launch, for meshes whose regions all fit on the chip at once, one per CU: a
 // workgroup carries its 64 x 32 region through all of them in registers, with a halo of all their layers (9 for
 // three taps and three L iterations, interior 46 x 14).  x1 and x2 never leave the workgroup and two of three
-// launches go, against 3.2 times the stencil work of the interior; with more regions than CUs that work, not
-// latency, is what counts.  130 x 118 x 3 in FP32: 24.1 us in three launches, 15.8 us in one.
+// launches go, against 3.2 times the stencil work of the interior, which counts when the regions take several rounds.
+// 130 x 118 x 3 in FP32: 24.1 us in three launches, 15.8 us in one.  Steps of 24 FGMRES iterations in FP64, three
+// launches and one: 252 regions (276 x 190 x 3) 1275 and 1050 us, 378 regions 1430 and 1284, 600 regions 1554 and 1653.
 // ------------------------------------------------------------------------------------------
-constexpr int kChebAllNP = 8, kChebAllNW = 4, kChebAllRegions = 256, kChebAllHalo = 10;
+constexpr int kChebAllNP = 8, kChebAllNW = 4, kChebAllHalo = 10;
 
 // SEP: x1 by the separable mass inverse of MR taps; else sM Chebyshev iterations (MR = 0)
 template <typename T, int MR>
@@ -519,7 +520,7 @@ static dim3 cheb_all_grid(const Dev& d, int mass_iters, int diff_iters, int mass
     if (halo > kChebAllHalo) return dim3(0);
     const int IX = kTX - 2 * halo, IY = kChebAllNP * kChebAllNW - 2 * halo;
     const long long n = (long long)((d.maxn[0] + IX - 1) / IX) * ((d.maxn[1] + IY - 1) / IY);
-    return n * d.S <= kChebAllRegions ? dim3((unsigned)n, d.S) : dim3(0);
+    return n * d.S <= d.cus ? dim3((unsigned)n, d.S) : dim3(0);
 }
 
 template <typename T, int RX, int RY, int NTH>
