@@ -38,11 +38,13 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
+from paper_1902_09761_amd.build import SOURCES  # noqa: E402
+
 METRIC = "amplitude DOF-steps/s at 1e-8 rel. residual + % HBM peak; plain vs mixed/batch"
 HBM_PEAK_GBS = 8000.0
 CSRC = os.path.join(ROOT, "paper_1902_09761_amd", "csrc")
-KERNEL_SOURCES = ["apfc_internal.h", "kernels_common.h", "kernels_region.h", "kernels.hip", "kernels_apply.hip",
-                  "kernels_cheb2d.hip", "kernels_mg.hip", "kernels_mass.hip"]
+# every file the kernels are compiled from: headers, then the sources in the order of the build
+KERNEL_SOURCES = sorted(f for f in os.listdir(CSRC) if f.endswith(".h")) + [f for f in SOURCES if f != "api.hip"]
 PROFILES = os.path.join(ROOT, "profiles")
 # kernel families with a byte model, as the library's probe names them, and the kernels they cover
 FAMILIES = {"cheb": "k_cheb2d (3D: k_cb_*)", "apply": "k_apply_dot2d/3d", "proj_final": "k_proj_final",
