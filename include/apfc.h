@@ -233,7 +233,8 @@ int apfc_step_adjoint(apfc_ctx* ctx, const apfc_state* before, const apfc_state*
 /* Apply one operator of the step to every instance: out_j = A_j in_j (which = APFC_OP_A, the
  * block matrix of Eq. (11) linearised at lin[].eta with step dt) or out_j = P_j^{-1} in_j
  * (which = APFC_OP_PINV, the block preconditioner of Eq. (12) by its four steps with the context's
- * inner solver and precision).  in/out hold (zeta, eta) pairs as [J][2][N] device arrays; lin is
+ * inner solver and precision; in FP64 the result is that of the inner iterations taken one by one to rounding,
+ * about 1e-15 of its largest entry, on smooth fields too).  in/out hold (zeta, eta) pairs as [J][2][N] device arrays; lin is
  * read only for APFC_OP_A.  For testing and for callers that drive their own Krylov method. */
 enum { APFC_OP_A = 0, APFC_OP_PINV = 1 };
 int apfc_apply(apfc_ctx* ctx, int which, const apfc_state* lin, const apfc_state* in, apfc_state* out,
@@ -279,7 +280,8 @@ int apfc_probe_read(apfc_ctx* ctx, int* launches, double* total_ms, double* byte
  * the first Gram-Schmidt pass), "residual", "proj_final" (the basis vector where the preconditioner does
  * not form it), "xupdate", "gs", "extrapolate", "rhs",
  * "mass" (the separable mass inverse on bricks), "mg" (multigrid V-cycle kernels), "pcg_spmv",
- * "pcg_update", "pcg_init", "pc_final", "reduce", "small", "other". */
+ * "pcg_update", "pcg_init", "pc_final", "reduce", "small", "other".  The 2D Jacobi-PCG kernels that take whole CG steps
+ * or solves per launch count as "pcg_spmv". */
 int apfc_probe_read_kernel(apfc_ctx* ctx, const char* name, int* launches, double* total_ms,
                            double* bytes_per_launch, long long* issued);
 

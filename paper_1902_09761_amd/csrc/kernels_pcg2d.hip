@@ -12,8 +12,9 @@ namespace apfc {
 // before it, applies OP to the new r and leaves its two sums, one partial of each per region.  Against 80-bit
 // arithmetic a P^{-1} is as accurate as with <p, OP p> summed in a pass of its own (2e-16 rms on amplitude fields).
 // Taking a solve's coefficients from the Gram matrix of its Krylov vectors would save launches, but loses up to eight
-// digits on smooth right-hand sides, where those vectors are nearly parallel; the sums over the new direction and
-// its image, expanded into ones known a launch earlier, lose a bit or two where the residual drops fast.
+// digits on smooth right-hand sides, where those vectors are nearly parallel.  The new <r, r> expanded into sums over
+// the old r and OP p (one launch per step as well) costs up to 1.4 times the error, where the residual drops fast, and
+// 1.4 times the launch with those sums in twice the precision.
 //
 // A workgroup holds a region of 64 x 8 NP nodes, interior plus kPcgHalo layers, in registers (row_sweep; one wave per
 // NP rows): OP p on the interior and one layer around it (instead of storing it), OP r on the interior.  Launches per

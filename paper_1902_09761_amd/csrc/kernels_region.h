@@ -120,6 +120,7 @@ struct RowStencil {
         return cM * M(A, B, C) + cK * K(A, B, C);
     }
 };
+
 struct SplitCoef {
     double a, b, c, d;
 };
