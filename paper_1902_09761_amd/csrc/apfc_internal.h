@@ -16,10 +16,10 @@ constexpr int kMaxJ = 8;
 constexpr int kMaxTerms = 24;
 constexpr int kMaxRestart = 32;
 constexpr int kMaxCheb = 64;     // Chebyshev iterations per inner solve
-// regions of the 2D Jacobi-PCG preconditioner with one launch per step: 64 columns x (8 waves of kPcgRows rows), kPcgHalo
-// layers of them halo, kPcgSums partials per region; up to kPcgMax iterations per inner solve
-constexpr int kPcgMax = 5, kPcgThreads = 512, kPcgHalo = 2, kPcgSums = 4;
-constexpr int kPcgRows[3] = {2, 4, 8};
+// regions of the 2D Jacobi-PCG preconditioner with one launch per step: 64 columns x (rows per wave, waves) of kPcgShape,
+// kPcgHalo layers of them halo, kPcgSums partials per region; up to kPcgMax iterations per inner solve
+constexpr int kPcgMax = 5, kPcgHalo = 2, kPcgSums = 4;
+constexpr int kPcgShape[3][2] = {{4, 4}, {8, 4}, {8, 8}};
 constexpr int kMassRMax = 4;     // taps per side of the separable mass inverse
 // bricks of the separable mass inverse and of the 3D Chebyshev L solves: 64 x kMassBY nodes per plane,
 // 512 threads; in 3D kBrickZShallow or kBrickZDeep planes (Dev::mbz)
@@ -229,9 +229,9 @@ void launch_precond_cheb(const Dev& d, int shape, const CTile* ctiles, int nctil
                          cx<T>* z, cx<T>* x1, cx<T>* x2, int mass_iters, int diff_iters, int mass_sep,
                          const VIn<T>& vin, const int* mask, hipStream_t st);
 
-// Jacobi-PCG inner solves, one launch per step, on regions of 64 x 8 rows nodes (rows of kPcgRows; tiles[].z = first
-// region of the tile's system).  w: five work vectors; part: 2 kPcgSums nreg doubles; v and z do not overlap.
-void launch_precond_pcg2d(const Dev& d, int rows, const CTile* tiles, int nreg, const zd* v, zd* z, zd* const* w,
+// Jacobi-PCG inner solves, one launch per step, on regions of kPcgShape[shape] (tiles[].z = first region of the tile's
+// system).  w: five work vectors; part: 2 kPcgSums nreg doubles; v and z do not overlap.
+void launch_precond_pcg2d(const Dev& d, int shape, const CTile* tiles, int nreg, const zd* v, zd* z, zd* const* w,
                           double* part, int mass_iters, int diff_iters, int mass_sep, const int* mask, hipStream_t st);
 // The same with one workgroup per system: every mesh at most 64 x 64 nodes.
 template <typename T>

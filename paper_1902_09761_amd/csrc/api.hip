@@ -132,7 +132,7 @@ struct apfc_ctx {
     int cheb_shape = 0;
     size_t max_ctiles = 0;
     std::vector<CTile> rtiles;         // regions of the fused 2D Jacobi-PCG preconditioner (empty: not used)
-    int pcg_rows = 0;                  // their rows per wave (kPcgRows)
+    int pcg_shape = 0;                 // their shape (kPcgShape)
     bool pcg_small = false;            // 2D Jacobi-PCG by one workgroup per system
     long long NT = 0, NI = 0;
     int maxn[3] = {1, 1, 1};           // largest mesh sizes over the systems
@@ -483,12 +483,10 @@ void build_ctiles(apfc_ctx& c) {
 
 // 2D Jacobi-PCG on many meshes of few rows: the launches per half-step share the chip by 16-row tiles, while one workgroup
 // per system (launch_precond_pcg_small, the same bits) takes 2.5 to 4.5 us per CG step and round of one workgroup per CU
-// however small the mesh, and the regions of launch_precond_pcg2d are 16 rows or more.  P^{-1} by the launches over
-// P^{-1} by workgroups, FP64, 3 + 5 + 5 steps:
+// however small the mesh.  P^{-1} by the launches over P^{-1} by workgroups, FP64, 3 + 5 + 5 steps:
 //   up to three systems per CU       4^2 1.2 to 2.8,  16^2 1.5 to 2.8,  64^2 2.3 to 3.7
 //   4 to 32 systems per CU           4^2 0.86 to 0.44, 12^2 1.09 to 0.81, 16^2 1.28 to 1.00, 20^2 1.9 to 1.7
-// with 1 + 1 + 1 steps 16^2 0.96 to 0.69, 20^2 1.17 to 1.00; FP32 alike.  By regions: 768 systems of 4^2 1.03,
-// 3072 of 66 x 4 0.72, of 16^2 1.15, of 66 x 20 2.3.
+// with 1 + 1 + 1 steps 16^2 0.96 to 0.69, 20^2 1.17 to 1.00; FP32 alike.
 bool many_tiny(const apfc_ctx& c) {
     long long tiles = 0, rows = 0;
     for (const Sys& y : c.sys) {
@@ -500,41 +498,38 @@ bool many_tiny(const apfc_ctx& c) {
 }
 
 // The 2D Jacobi-PCG preconditioner's kernels, and the regions of launch_precond_pcg2d (one launch per step): FP64 and up
-// to kPcgMax iterations per inner solve, where it was compared with the two launches per step that sum <p, OP p> in a pass of its own (kernels_pcg2d.hip).  In
-// FP32 storage with long restarts the rounding of z decides how far below rtol a solve ends, and CG's own rounding is
-// kept there.  Meshes of at most 64 x 64 nodes go to launch_precond_pcg_small, batches of
-// many tiny ones to the launches per half-step.
-// Rows per wave (kPcgRows): the fewest that leave at most one region per CU, where latency counts and a taller region
-// takes longer (P^{-1} of 180 x 170 x 3 by 2, 4, 8 rows: 104, 120, 150 us; 320^2 x 3: 150, 143, 178; 512^2 x 3: 295, 260,
-// 237).  Where none does, 4 rows (1024^2 x 3: 1237, 842, 840 us; 24 meshes of 250 x 234 x 3: 1228, 1166, 1267), or 8 on
-// systems of more than 2^20 nodes, where the halo's share of the traffic counts (1200^2 x 3 by 4, 8 rows: 1308, 1239 us;
-// 2048^2 x 3: 5137, 4090).
+// to kPcgMax iterations per inner solve, where it was compared with the two launches per step that sum <p, OP p> in a
+// pass of its own (kernels_pcg2d.hip).  In FP32 storage with long restarts the rounding of z decides how far below rtol
+// a solve ends, and CG's own rounding is kept there.  Meshes of at most 64 x 64 nodes go to launch_precond_pcg_small
+// (batches of many tiny ones to the launches per half-step); wider ones of few rows go by regions (launches over
+// regions: 3072 systems of 66 x 4 1.22, of 66 x 8 1.60, of 66 x 16 1.08; 12285 of 4^2 and three of 66 x 4 0.95).
+// Region rows (kPcgShape: 16, 32, 64 with the halo): 16 up to four regions per CU, where latency counts, and for systems
+// of less than 2^15 nodes, which leave less of it empty; 64 above 2^20 nodes per system, where the halo's share of the
+// traffic counts; else 32.  P^{-1} by 16, 32, 64 rows: 250 x 234 x 3 125, 137, 166 us; 400^2 x 3 176, 193, 191; 512^2 x 3
+// 253, 246, 237; 1024^2 x 3 1036, 792, 864; 2048^2 x 3 7576, 4535, 4096; 96 meshes of 130 x 118 x 3 1229, 1331, 1433; 100 of
+// 250 x 234 x 3 4558, 4546, 5052.
 // The region table lies in the work vector pc[5] and the partials in apart, which the two-launch path uses otherwise.
 CTile* rtile_table(const apfc_ctx& c) { return (CTile*)c.pc[5]; }
 void choose_pcg(apfc_ctx& c) {
     c.rtiles.clear();
     const apfc_params& p = c.solver;
     c.pcg_small = false;
-    if (c.dim != 2 || p.inner_kind != APFC_INNER_PCG || many_tiny(c)) return;
-    c.pcg_small = c.maxn[0] <= kTX && c.maxn[1] <= kTX;
-    if (c.pcg_small || p.diff_iters > kPcgMax || (p.mass_kind != APFC_MASS_SEPARABLE && p.mass_iters > kPcgMax) || c.mixed)
+    if (c.dim != 2 || p.inner_kind != APFC_INNER_PCG) return;
+    const bool small = c.maxn[0] <= kTX && c.maxn[1] <= kTX;
+    c.pcg_small = small && !many_tiny(c);
+    if (small || p.diff_iters > kPcgMax || (p.mass_kind != APFC_MASS_SEPARABLE && p.mass_iters > kPcgMax) || c.mixed)
         return;
     const int IX = kTX - 2 * kPcgHalo;
-    auto interior = [](int rows) { return rows * (kPcgThreads / 64) - 2 * kPcgHalo; };
-    auto count = [&](int rows) {
-        const int IY = interior(rows);
+    auto interior = [](int shape) { return kPcgShape[shape][0] * kPcgShape[shape][1] - 2 * kPcgHalo; };
+    auto count = [&](int shape) {
+        const int IY = interior(shape);
         long long n = 0;
         for (const Sys& y : c.sys) n += (long long)((y.nx + IX - 1) / IX) * ((y.ny + IY - 1) / IY);
         return n;
     };
-    c.pcg_rows = c.NT > (1LL << 20) * c.S ? kPcgRows[2] : kPcgRows[1];
-    for (int rows : kPcgRows)
-        if (count(rows) <= c.cus) {
-            c.pcg_rows = rows;
-            break;
-        }
-    if (2 * kPcgSums * count(c.pcg_rows) > (2LL * kMaxRestart + 2) * c.max_tiles) return;
-    const int IY = interior(c.pcg_rows);
+    c.pcg_shape = count(0) <= 4LL * c.cus || c.NT < (1LL << 15) * c.S ? 0 : c.NT <= (1LL << 20) * c.S ? 1 : 2;
+    if (2 * kPcgSums * count(c.pcg_shape) > (2LL * kMaxRestart + 2) * c.max_tiles) return;
+    const int IY = interior(c.pcg_shape);
     for (int s = 0; s < c.S; ++s) {
         const Sys& y = c.sys[s];
         std::vector<CTile> nat;
@@ -1192,7 +1187,7 @@ void precond(apfc_ctx* c, const Dev& d, const cx<T>* v, cx<T>* z, const int* mas
         launch_precond_pcg_small<T>(d, v, z, pc[0], pc[1], c->solver.mass_iters, c->solver.diff_iters, sep, mask, st);
     else if (std::is_same_v<T, double> && !c->rtiles.empty()) {
         if constexpr (std::is_same_v<T, double>)
-            launch_precond_pcg2d(d, c->pcg_rows, rtile_table(*c), (int)c->rtiles.size(), v, z, (zd**)c->pc,
+            launch_precond_pcg2d(d, c->pcg_shape, rtile_table(*c), (int)c->rtiles.size(), v, z, (zd**)c->pc,
                                  c->apart, c->solver.mass_iters, c->solver.diff_iters, sep, mask, st);
     } else
         launch_precond<T>(d, v, z, pc[0], pc[1], pc[2], pc[3], pc[4], pc[5], c->tpart, c->solver.mass_iters,

@@ -16,8 +16,8 @@ namespace apfc {
 // the old r and OP p (one launch per step as well) costs up to 1.4 times the error, where the residual drops fast, and
 // 1.4 times the launch with those sums in twice the precision.
 //
-// A workgroup holds a region of 64 x 8 NP nodes, interior plus kPcgHalo layers, in registers (row_sweep; one wave per
-// NP rows): OP p on the interior and one layer around it (instead of storing it), OP r on the interior.  Launches per
+// A workgroup holds a region of 64 x (NW NP) nodes, interior plus kPcgHalo layers, in registers (row_sweep; one wave
+// per NP rows): OP p on the interior and one layer around it (instead of storing it), OP r on the interior.  Launches per
 // application of P^{-1}, K steps per solve:
 //   PCG_MASS  r = beta1                                              (SEP: x1 given)
 //   PCG_STEP  K - 1 times
@@ -27,8 +27,8 @@ namespace apfc {
 //   PCG_STEP  K - 1 times
 //   PCG_END   last step's chi2; step 4
 // K = 3 and 5: 14 launches instead of the 30 of two launches per step.  Small meshes are bound by launches and latency
-// (96 x 80 x 3: 174 us -> 91 us), large ones by memory: a step moves 6 vectors instead of 10 (1024^2 x 3: 1568 us ->
-// 842 us; 2048^2 x 3: 12.0 ms -> 4.1 ms).
+// (96 x 80 x 3: 174 us -> 95 us), large ones by memory: a step moves 6 vectors instead of 10 (1024^2 x 3: 1568 us ->
+// 805 us; 2048^2 x 3: 12.0 ms -> 4.1 ms).
 // ------------------------------------------------------------------------------------------
 enum { PCG_MASS, PCG_STEP, PCG_G, PCG_M, PCG_END };
 
@@ -43,13 +43,13 @@ struct PcgVecs {
 
 // Partials of a region b: g[b] = <r, r>, g[nreg + b] = <r, OP r>; at a system's first region also its <r, r> and alpha
 // of the step before, g[2 nreg + b] and g[3 nreg + b].
-template <int NP, int KIND, bool isM>
-__global__ __launch_bounds__(kPcgThreads) void k_pcg2d(const Sys* sys, const CTile* tiles, const int* mask, const PcgVecs a,
-                                                      const zd* v, zd* z, long long NT, const double* gin, double* gout,
-                                                      int nreg) {
+template <int NP, int NW, int KIND, bool isM>
+__global__ __launch_bounds__(64 * NW) void k_pcg2d(const Sys* sys, const CTile* tiles, const int* mask, const PcgVecs a,
+                                                  const zd* v, zd* z, long long NT, const double* gin, double* gout,
+                                                  int nreg) {
     using T = double;
     using Row = RowStencil<T>::Row;
-    constexpr int NW = kPcgThreads / 64, IX = kTX - 2 * kPcgHalo, IY = NP * NW - 2 * kPcgHalo;
+    constexpr int IX = kTX - 2 * kPcgHalo, IY = NP * NW - 2 * kPcgHalo;
     __shared__ zd edges[2][NW][2][kTX];
     __shared__ double sums[2], part[NW][2];
     const CTile tile = tiles[blockIdx.x];
@@ -403,7 +403,7 @@ template void launch_precond_pcg_small<double>(const Dev&, const zd*, zd*, zd*, 
 template void launch_precond_pcg_small<float>(const Dev&, const zf*, zf*, zf*, zf*, int, int, int, const int*,
                                               hipStream_t);
 
-template <int NP>
+template <int NP, int NW>
 static void pcg_launches(const Dev& d, const CTile* tiles, int nreg, const zd* v, zd* z, zd* const* w, double* part,
                          int mass_iters, int diff_iters, int mass_sep, const int* mask, hipStream_t st) {
     using std::integral_constant;
@@ -414,8 +414,8 @@ static void pcg_launches(const Dev& d, const CTile* tiles, int nreg, const zd* v
     int g = 0;
     auto go = [&](auto kind, auto mass, double vecs) {
         ProbeScope ps(d, KID_PCG_SPMV, st, vec * vecs, mask, true);
-        ps.launch(k_pcg2d<NP, decltype(kind)::value, decltype(mass)::value>, dim3(nreg), dim3(kPcgThreads), d.sys, tiles,
-                  mask, a, v, z, d.NT, G[g], G[g ^ 1], nreg);
+        ps.launch(k_pcg2d<NP, NW, decltype(kind)::value, decltype(mass)::value>, dim3(nreg), dim3(64 * NW), d.sys,
+                  tiles, mask, a, v, z, d.NT, G[g], G[g ^ 1], nreg);
         g ^= 1;
     };
     // steps 1 .. n - 1 of a solve for the right-hand side r, whose sums the launch before has left
@@ -453,14 +453,17 @@ static void pcg_launches(const Dev& d, const CTile* tiles, int nreg, const zd* v
     go(integral_constant<int, PCG_END>{}, std::false_type{}, a.p ? 7.0 : 5.0);
 }
 
-void launch_precond_pcg2d(const Dev& d, int rows, const CTile* tiles, int nreg, const zd* v, zd* z, zd* const* w, double* part,
-                          int mass_iters, int diff_iters, int mass_sep, const int* mask, hipStream_t st) {
-    if (rows == kPcgRows[0])
-        pcg_launches<kPcgRows[0]>(d, tiles, nreg, v, z, w, part, mass_iters, diff_iters, mass_sep, mask, st);
-    else if (rows == kPcgRows[1])
-        pcg_launches<kPcgRows[1]>(d, tiles, nreg, v, z, w, part, mass_iters, diff_iters, mass_sep, mask, st);
-    else
-        pcg_launches<kPcgRows[2]>(d, tiles, nreg, v, z, w, part, mass_iters, diff_iters, mass_sep, mask, st);
+void launch_precond_pcg2d(const Dev& d, int shape, const CTile* tiles, int nreg, const zd* v, zd* z, zd* const* w,
+                          double* part, int mass_iters, int diff_iters, int mass_sep, const int* mask, hipStream_t st) {
+    auto go = [&](auto i) {
+        constexpr int I = decltype(i)::value;
+        pcg_launches<kPcgShape[I][0], kPcgShape[I][1]>(d, tiles, nreg, v, z, w, part, mass_iters, diff_iters, mass_sep, mask,
+                                                       st);
+    };
+    static_assert(sizeof(kPcgShape) / sizeof(kPcgShape[0]) == 3, "one case per shape");
+    if (shape == 0) go(std::integral_constant<int, 0>{});
+    else if (shape == 1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 2>{});
 }
 
 }  // namespace apfc

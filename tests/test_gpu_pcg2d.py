@@ -92,7 +92,6 @@ def test_one_workgroup_narrow_and_tall(n):
     ((8, 8), 256, (3, 5), True),       # three systems per CU
     ((8, 8), 300, (3, 5), False), ((4, 5), 400, (1, 1), False), ((16, 16), 300, (1, 1), False),
     ((16, 16), 300, (3, 5), True), ((7, 17), 300, (1, 1), True),
-    ((66, 5), 300, (3, 5), False),
 ])
 @pytest.mark.parametrize("precision,tol", [(apfc.APFC_FP64, TOL), (apfc.APFC_MIXED, 2e-5)])
 def test_many_tiny_meshes(n, count, its, small, precision, tol):
@@ -149,7 +148,7 @@ def test_smooth_right_hand_sides(kind, n, its, dt):
 
 @pytest.mark.parametrize("mass", ["iter", "sep"])
 @pytest.mark.parametrize("its", [(1, 1), (2, 1), (1, 2), (2, 2)])
-@pytest.mark.parametrize("n", [(121, 25), (250, 234), (421, 400)])    # 2, 4 and 8 rows per wave
+@pytest.mark.parametrize("n", [(121, 25), (250, 234), (530, 500)])    # regions of 16, 16 and 32 rows
 def test_shapes_of_the_step_sequence(n, its, mass):
     """Solves of one and two steps, whose first and last steps take other vectors than those between."""
     m = [_mesh(n)]
@@ -157,8 +156,15 @@ def test_shapes_of_the_step_sequence(n, its, mass):
     assert _worst(m, pairs, _pinv(m, pairs, its, mass), its, mass) <= TOL
 
 
+def test_more_than_a_million_nodes():
+    """Regions of 64 rows."""
+    m = [_mesh((1040, 1012))]
+    pairs = _random(m, 51)
+    assert _worst(m, pairs, _pinv(m, pairs, (2, 3)), (2, 3)) <= TOL
+
+
 def test_large_meshes_in_a_batch():
-    """More regions than CUs whatever their rows: four rows per wave, uneven systems."""
+    """Many regions, uneven systems (regions of 32 rows)."""
     m = [_mesh(n) for n in ((250, 234), (40, 28), (300, 260), (256, 512), (190, 310), (64, 64), (380, 220), (301, 299))]
     pairs = _random(m, 47)
     assert _worst(m, pairs, _pinv(m, pairs, (3, 5)), (3, 5)) <= TOL
